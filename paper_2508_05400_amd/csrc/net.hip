@@ -14,144 +14,340 @@
 
 namespace {
 
-__global__ __launch_bounds__(256) void k_conv_fwd(const float* __restrict__ x, const float* __restrict__ w,
-                                                  const float* __restrict__ bias, float* __restrict__ y, int B, int C,
-                                                  int O, int H, int W, int dil, int relu) {
-  const int64_t total = (int64_t)B * O * H * W;
-  for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-       idx += (int64_t)gridDim.x * blockDim.x) {
-    const int j = (int)(idx % W);
-    const int i = (int)((idx / W) % H);
-    const int o = (int)((idx / ((int64_t)W * H)) % O);
-    const int b = (int)(idx / ((int64_t)W * H * O));
-    float acc = bias[o];
-    for (int c = 0; c < C; ++c) {
-      const float* xc = x + ((int64_t)b * C + c) * H * W;
-      const float* wc = w + ((int64_t)o * C + c) * 9;
-#pragma unroll
-      for (int di = 0; di < 3; ++di) {
-        const int ii = i + dil * (di - 1);
-        if (ii < 0 || ii >= H) continue;
-#pragma unroll
-        for (int dj = 0; dj < 3; ++dj) {
-          const int jj = j + dil * (dj - 1);
-          if (jj < 0 || jj >= W) continue;
-          acc += wc[di * 3 + dj] * xc[ii * W + jj];
-        }
-      }
+// A 3x3 dilated convolution with zero padding, in both directions.
+//   forward (BWD = false): in = x, out(o) = bias[o] + sum over c, taps of w[o, c, tap] x(c, p + offset(tap)), ReLU
+//   data gradient (BWD):   in = g, out(c) = sum over o, taps of w[o, c, tap] g(o, p - offset(tap)),
+//                          g = dy, masked by y > 0 when RELU (act = y)
+// One output is one chain of fused multiply-adds (input channels in order,
+// taps in order), whatever OT and CU.
+// A tap outside the image adds nothing: its input is taken as 0, which leaves
+// the sum as it is unless a weight is infinite or NaN; a sum that ends
+// infinite or NaN is formed again with those taps left out (conv_masked).
+template <bool BWD, bool RELU>
+__device__ __attribute__((noinline)) float conv_masked(const float* __restrict__ xb, const float* __restrict__ ab,
+                                                       const float* __restrict__ w, float acc, int o, int CI, int CO,
+                                                       int HW, int H, int W, int i, int j, int dil) {
+  for (int c = 0; c < CI; ++c)
+    for (int t = 0; t < 9; ++t) {
+      const int di = BWD ? 1 - t / 3 : t / 3 - 1, dj = BWD ? 1 - t % 3 : t % 3 - 1;
+      const int ii = i + dil * di, jj = j + dil * dj;
+      if (ii < 0 || ii >= H || jj < 0 || jj >= W) continue;
+      const int64_t e = (int64_t)c * HW + ii * W + jj;
+      float v = xb[e];
+      if (BWD && RELU && !(ab[e] > 0.f)) v = 0.f;
+      acc = __builtin_fmaf(BWD ? w[((int64_t)c * CO + o) * 9 + t] : w[((int64_t)o * CI + c) * 9 + t], v, acc);
     }
-    y[idx] = (relu && acc < 0.f) ? 0.f : acc;
-  }
+  return acc;
 }
 
-// g = dy masked by the layer's ReLU (y > 0) when relu; dx = transposed convolution of g.
-__global__ __launch_bounds__(256) void k_conv_bwd_data(const float* __restrict__ dy, const float* __restrict__ y,
-                                                       const float* __restrict__ w, float* __restrict__ dx, int B,
-                                                       int C, int O, int H, int W, int dil, int relu) {
-  const int64_t total = (int64_t)B * C * H * W;
+// Reads at byte offsets from a pointer that all lanes share, 0 for an offset
+// past the end.  With 32-bit offsets (IT = uint32_t, for tensors under 1 GiB;
+// n its elements) they are buffer loads, for which the hardware does that:
+// nothing has to be done to the value (and hence waited for) after the load.
+// A row and a column outside the image add kOutRow and kOutCol to the offset,
+// which keep any sum of an offset and one or both past the end.
+template <typename IT>
+struct Plane {  // tensors of any size
+  static constexpr IT kOutRow = (IT)1 << (8 * sizeof(IT) - 1), kOutCol = kOutRow >> 1;
+  const float* p;
+  __device__ __forceinline__ Plane(const float* q, int64_t) : p(q) {}
+  __device__ __forceinline__ float get(IT off) const {
+    return off >= kOutCol ? 0.f : *(const float*)((const char*)p + off);
+  }
+};
+template <>
+struct Plane<uint32_t> {
+  static constexpr uint32_t kOutRow = 0x80000000u, kOutCol = 0x40000000u;
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ Plane(const float* q, int64_t n)
+      : r(__builtin_amdgcn_make_buffer_rsrc((void*)q, 0, (int)(4 * n), 0x00027000)) {}
+  __device__ __forceinline__ float get(uint32_t off) const {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+  }
+};
+
+// A lane owns one pixel and OT output channels, so an input value is loaded
+// once per tap for OT products, and the weights, which all lanes share, come
+// through scalar loads; the nine taps of CU input channels are loaded before
+// their first product (from addresses clamped into the image), contiguous
+// across a wave.
+template <int OT, int CU, bool BWD, bool RELU, typename IT>
+__global__ __launch_bounds__(256) void k_conv(const float* __restrict__ in, const float* __restrict__ act,
+                                              const float* __restrict__ w, const float* __restrict__ bias,
+                                              float* __restrict__ out, int B, int CI, int CO, int H, int W, int dil) {
+  const int HW = H * W;
+  const int64_t total = (int64_t)B * HW;
+  const int q0 = (int)(blockIdx.z * gridDim.y + blockIdx.y) * OT;  // first output channel
+  if (q0 >= CO) return;
   for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
        idx += (int64_t)gridDim.x * blockDim.x) {
-    const int j = (int)(idx % W);
-    const int i = (int)((idx / W) % H);
-    const int c = (int)((idx / ((int64_t)W * H)) % C);
-    const int b = (int)(idx / ((int64_t)W * H * C));
-    float acc = 0.f;
-    for (int o = 0; o < O; ++o) {
-      const int64_t base = ((int64_t)b * O + o) * H * W;
-      const float* wc = w + ((int64_t)o * C + c) * 9;
+    const int b = sizeof(IT) == 4 ? (int)((uint32_t)idx / (uint32_t)HW) : (int)(idx / HW);
+    const int pix = (int)(idx - (int64_t)b * HW);
+    const int i = pix / W, j = pix - i * W;
+    IT off[9];
+    {
+      IT ro[3], co[3];
 #pragma unroll
-      for (int di = 0; di < 3; ++di) {
-        const int ii = i - dil * (di - 1);
-        if (ii < 0 || ii >= H) continue;
+      for (int t = 0; t < 3; ++t) {
+        const int ii = i + dil * (BWD ? 1 - t : t - 1), jj = j + dil * (BWD ? 1 - t : t - 1);
+        ro[t] = ii >= 0 && ii < H ? ((IT)b * CI * HW + (IT)ii * W) * 4 : Plane<IT>::kOutRow;
+        co[t] = jj >= 0 && jj < W ? (IT)jj * 4 : Plane<IT>::kOutCol;
+      }
 #pragma unroll
-        for (int dj = 0; dj < 3; ++dj) {
-          const int jj = j - dil * (dj - 1);
-          if (jj < 0 || jj >= W) continue;
-          const int64_t p = base + ii * W + jj;
-          float g = dy[p];
-          if (relu && !(y[p] > 0.f)) g = 0.f;
-          acc += wc[di * 3 + dj] * g;
+      for (int t = 0; t < 9; ++t) off[t] = ro[t / 3] + co[t % 3];
+    }
+    float acc[OT];
+#pragma unroll
+    for (int q = 0; q < OT; ++q) acc[q] = BWD ? 0.f : bias[q0 + q < CO ? q0 + q : CO - 1];
+    for (int c0 = 0; c0 < CI; c0 += CU) {
+      float v[CU][9];
+#pragma unroll
+      for (int u = 0; u < CU; ++u) {
+        const int64_t ch = (int64_t)(c0 + u < CI ? c0 + u : CI - 1) * HW;
+        const Plane<IT> pi(in + ch, total * CI - ch);
+#pragma unroll
+        for (int t = 0; t < 9; ++t) v[u][t] = pi.get(off[t]);
+        if constexpr (RELU && BWD) {
+          const Plane<IT> pa(act + ch, total * CI - ch);
+          float av[9];
+#pragma unroll
+          for (int t = 0; t < 9; ++t) av[t] = pa.get(off[t]);
+#pragma unroll
+          for (int t = 0; t < 9; ++t) v[u][t] = av[t] > 0.f ? v[u][t] : 0.f;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < CU; ++u) {
+        const int c = c0 + u;
+        if (c < CI) {
+#pragma unroll
+          for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int q = 0; q < OT; ++q) {
+              const int o = q0 + q < CO ? q0 + q : CO - 1;
+              const float wt = BWD ? w[((int64_t)c * CO + o) * 9 + t] : w[((int64_t)o * CI + c) * 9 + t];
+              acc[q] = __builtin_fmaf(wt, v[u][t], acc[q]);
+            }
         }
       }
     }
-    dx[idx] = acc;
+    float* ob = out + (int64_t)b * CO * HW + pix;
+#pragma unroll
+    for (int q = 0; q < OT; ++q)
+      if (q0 + q < CO) {
+        float s = acc[q];
+        if (!__builtin_isfinite(s))
+          s = conv_masked<BWD, RELU>(in + (int64_t)b * CI * HW, RELU && BWD ? act + (int64_t)b * CI * HW : nullptr, w,
+                                     BWD ? 0.f : bias[q0 + q], q0 + q, CI, CO, HW, H, W, i, j, dil);
+        ob[(int64_t)(q0 + q) * HW] = (!BWD && RELU && s < 0.f) ? 0.f : s;
+      }
   }
 }
 
 // dw[o, c, tap] = sum_{b, pixel} g[b, o, pixel] x[b, c, pixel + offset(tap)];
-// db[o] = sum g[b, o, :].  One block per (o, c); fixed-order block reduction.
+// db[o] = sum g[b, o, :] (g = dy, masked by y > 0 when RELU).  Every sum is
+// 256 chains of fused multiply-adds (chain t takes the pixels t, t + 256, ...
+// of the whole batch in order, leaving out g = 0 and taps outside the image),
+// added by a fixed tree, so it does not depend on how the work is split.
+// One chain of dw with g = 0 and outside taps left out one by one: for sums
+// that came out infinite or NaN (see k_conv_bwd_filter).
+template <bool RELU>
+__device__ __attribute__((noinline)) float filter_masked(const float* __restrict__ x, const float* __restrict__ dy,
+                                                         const float* __restrict__ y, int B, int C, int O, int H,
+                                                         int W, int dil, int c, int o, int t, int chain) {
+  const int HW = H * W;
+  float acc = 0.f;
+  for (int64_t q = chain; q < (int64_t)B * HW; q += 256) {
+    const int64_t b = q / HW;
+    const int pix = (int)(q - b * HW);
+    const int64_t e = (b * O + o) * HW + pix;
+    float g = dy[e];
+    if (RELU && !(y[e] > 0.f)) g = 0.f;
+    if (g == 0.f) continue;
+    const int ii = pix / W + dil * (t / 3 - 1), jj = pix % W + dil * (t % 3 - 1);
+    if (ii >= 0 && ii < H && jj >= 0 && jj < W)
+      acc = __builtin_fmaf(g, x[(b * C + c) * HW + ii * W + jj], acc);
+  }
+  return acc;
+}
+
+// A workgroup owns OT output channels, one input channel and NT taps (9, or
+// the 3 of one row of the filter); its thread t runs chain t of all of them,
+// with the loads of U pixels issued before the first product.  Taps outside
+// the image read a clamped address and count as x = 0.  g = 0 and x = 0 leave
+// a finite sum as it is; a chain that ends infinite or NaN is run again with
+// them left out.
+template <int OT, int NT, int U, bool RELU, typename IT, bool TINY>
 __global__ __launch_bounds__(256) void k_conv_bwd_filter(const float* __restrict__ x, const float* __restrict__ dy,
                                                          const float* __restrict__ y, float* __restrict__ dw,
                                                          float* __restrict__ db, int B, int C, int O, int H, int W,
-                                                         int dil, int relu) {
-  const int o = blockIdx.x / C, c = blockIdx.x % C;
-  float acc[10];
+                                                         int dil) {
+  constexpr int NR3 = NT / 3;
+  const int HW = H * W;
+  const int tg = blockIdx.x % (9 / NT), oc = blockIdx.x / (9 / NT);
+  const int c = oc % C, o0 = oc / C * OT, t0 = tg * NT;
+  const int64_t npix = (int64_t)B * HW;
+  float acc[OT][NT], ab[OT];
 #pragma unroll
-  for (int t = 0; t < 10; ++t) acc[t] = 0.f;
-  const int64_t npix = (int64_t)B * H * W;
-  for (int64_t q = threadIdx.x; q < npix; q += blockDim.x) {
-    const int b = (int)(q / ((int64_t)H * W));
-    const int pix = (int)(q % ((int64_t)H * W));
-    const int i = pix / W, j = pix % W;
-    const int64_t p = ((int64_t)b * O + o) * H * W + pix;
-    float g = dy[p];
-    if (relu && !(y[p] > 0.f)) g = 0.f;
-    if (g == 0.f) continue;
-    const float* xc = x + ((int64_t)b * C + c) * H * W;
+  for (int k = 0; k < OT; ++k) {
+    ab[k] = 0.f;
 #pragma unroll
-    for (int di = 0; di < 3; ++di) {
-      const int ii = i + dil * (di - 1);
+    for (int t = 0; t < NT; ++t) acc[k][t] = 0.f;
+  }
+  // the chain's pixel: column j, row offset rw = W i, and the byte offsets
+  // xo, go of its sample in x and dy; one step is 256 pixels
+  const int sj = 256 % W, srw = 256 / W * W;
+  const int drow = (dil < H ? dil : H) * W, dcol = dil < W ? dil : W;
+  const int p0 = (int)threadIdx.x % HW;
+  int j = p0 % W, rw = p0 - j;
+  const IT xs = (IT)C * HW * 4, gs = (IT)O * HW * 4;
+  IT xo = (IT)((int)threadIdx.x / HW) * xs, go = (IT)((int)threadIdx.x / HW) * gs;
+  const float* xc = x + (int64_t)c * HW;
+  const Plane<IT> px(xc, npix * C - (int64_t)c * HW);
+  auto load = [&](int64_t q, float(&g)[U][OT], float(&yv)[U][OT], float(&v)[U][NT]) {
 #pragma unroll
-      for (int dj = 0; dj < 3; ++dj) {
-        const int jj = j + dil * (dj - 1);
-        if (ii >= 0 && ii < H && jj >= 0 && jj < W) acc[di * 3 + dj] += g * xc[ii * W + jj];
+    for (int u = 0; u < U; ++u) {
+      const bool in = (IT)q + 256 * u < (IT)npix;
+      const IT gb = in ? go + (IT)(rw + j) * 4 : Plane<IT>::kOutRow;
+#pragma unroll
+      for (int k = 0; k < OT; ++k) {
+        const int64_t ch = (int64_t)(o0 + k < O ? o0 + k : O - 1) * HW;
+        g[u][k] = Plane<IT>(dy + ch, npix * O - ch).get(gb);
+        yv[u][k] = RELU ? Plane<IT>(y + ch, npix * O - ch).get(gb) : 1.f;
+      }
+      // the pixel's own row is in the image; the ones drow away are if they do not leave [0, HW)
+      const IT xb = in ? xo : Plane<IT>::kOutRow;
+      const IT co[3] = {j >= dcol ? (IT)(j - dcol) * 4 : Plane<IT>::kOutCol, (IT)j * 4,
+                        j + dcol < W ? (IT)(j + dcol) * 4 : Plane<IT>::kOutCol};
+#pragma unroll
+      for (int r = 0; r < NR3; ++r) {
+        const int e = t0 / 3 + r - 1;
+        const int rr = rw + drow * e;
+        IT ro = xb + (IT)rr * 4;
+        if (e < 0) ro = rr >= 0 ? ro : Plane<IT>::kOutRow;
+        if (e > 0) ro = rr < HW ? ro : Plane<IT>::kOutRow;
+#pragma unroll
+        for (int t = 0; t < 3; ++t) v[u][3 * r + t] = px.get(ro + co[t]);
+      }
+      j += sj;
+      rw += srw;
+      const int cj = j >= W ? W : 0;
+      j -= cj;
+      rw += cj;
+      if (TINY) {
+        while (rw >= HW) {
+          rw -= HW;
+          xo += xs;
+          go += gs;
+        }
+      } else {
+        const bool cr = rw >= HW;
+        rw -= cr ? HW : 0;
+        xo += cr ? xs : 0;
+        go += cr ? gs : 0;
       }
     }
-    acc[9] += g;
-  }
-  __shared__ float red[10][256];
+  };
+  auto add = [&](const float(&dv)[U][OT], const float(&yv)[U][OT], const float(&v)[U][NT]) {
 #pragma unroll
-  for (int t = 0; t < 10; ++t) red[t][threadIdx.x] = acc[t];
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s)
-      for (int t = 0; t < 10; ++t) red[t][threadIdx.x] += red[t][threadIdx.x + s];
-    __syncthreads();
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < OT; ++k) {
+        const float g = yv[u][k] > 0.f ? dv[u][k] : 0.f;
+        ab[k] += g;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[k][t] = __builtin_fmaf(g, v[u][t], acc[k][t]);
+      }
+  };
+  // two sets of registers: the next U pixels load while the current ones are added
+  float g0[U][OT], y0[U][OT], v0[U][NT], g1[U][OT], y1[U][OT], v1[U][NT];
+  load(threadIdx.x, g0, y0, v0);
+  for (int64_t q = threadIdx.x; q < npix; q += 512 * U) {
+    load(q + 256 * U, g1, y1, v1);
+    __builtin_amdgcn_sched_barrier(0);
+    add(g0, y0, v0);
+    load(q + 512 * U, g0, y0, v0);
+    __builtin_amdgcn_sched_barrier(0);
+    add(g1, y1, v1);
   }
-  if (threadIdx.x < 9) dw[((int64_t)o * C + c) * 9 + threadIdx.x] = red[threadIdx.x][0];
-  if (threadIdx.x == 9 && c == 0) db[o] = red[9][0];
+#pragma unroll
+  for (int k = 0; k < OT; ++k)
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      if (!__builtin_isfinite(acc[k][t]) && o0 + k < O)
+        acc[k][t] = filter_masked<RELU>(x, dy, y, B, C, O, H, W, dil, c, o0 + k, t0 + t, threadIdx.x);
+  // the tree over the chains: 128, 64, then 32 .. 1 apart
+  constexpr int NR = OT * (NT + 1);
+  __shared__ float red[NR][256];
+#pragma unroll
+  for (int k = 0; k < OT; ++k) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) red[k * (NT + 1) + t][threadIdx.x] = acc[k][t];
+    red[k * (NT + 1) + NT][threadIdx.x] = ab[k];
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  for (int r = wv; r < NR; r += 4) {
+    float s = (red[r][lane] + red[r][lane + 128]) + (red[r][lane + 64] + red[r][lane + 192]);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) s += __shfl_down(s, d);
+    const int o = o0 + r / (NT + 1), t = r % (NT + 1);
+    if (lane == 0 && o < O) {
+      if (t < NT) dw[((int64_t)o * C + c) * 9 + t0 + t] = s;
+      else if (c == 0 && tg == 0) db[o] = s;
+    }
+  }
 }
 
 // Per sample b: loss[b] = 1 - ||V_b^T u_b||^2/||u_b||^2 and
-// du_b = -2 (V_b V_b^T u_b - rho u_b) / ||u_b||^2 / B.  One block per sample.
-__global__ __launch_bounds__(256) void k_subspace_loss(const float* __restrict__ u, const float* __restrict__ V,
-                                                       float* __restrict__ loss, float* __restrict__ du, int B,
-                                                       int P, int K) {
-  constexpr int KM = 32;
+// du_b = -2 (V_b V_b^T u_b - rho u_b) / ||u_b||^2 / B.  One block per sample:
+// each inner product is 256 chains (chain t takes p = t, t + 256, ...) and a
+// fixed tree; four groups of 256 threads share the columns, and the loads of
+// four p go out together (the samples are few, so the kernel is bound by
+// latency: 23 us, 35 us with one group and one p at a time, for 32 samples of
+// 4096 x 17).
+__global__ __launch_bounds__(1024) void k_subspace_loss(const float* __restrict__ u, const float* __restrict__ V,
+                                                        float* __restrict__ loss, float* __restrict__ du, int B,
+                                                        int P, int K) {
+  constexpr int KM = 32, KG = KM / 4, U = 4;
   const int b = blockIdx.x;
   const float* ub = u + (int64_t)b * P;
   const float* Vb = V + (int64_t)b * P * K;
   __shared__ float red[KM + 1][256];
   __shared__ float pk[KM + 1];
-  float acc[KM + 1];
+  const int t = threadIdx.x & 255, kg = threadIdx.x >> 8;  // columns kg, kg + 4, ...
+  float acc[KG], uu0 = 0.f;
 #pragma unroll
-  for (int k = 0; k <= KM; ++k) acc[k] = 0.f;
-  for (int p = threadIdx.x; p < P; p += blockDim.x) {
-    const float up = ub[p];
+  for (int k = 0; k < KG; ++k) acc[k] = 0.f;
+  for (int p = t; p < P; p += 256 * U) {
+    float up[U], v[U][KG];
 #pragma unroll
-    for (int k = 0; k < KM; ++k)
-      if (k < K) acc[k] += Vb[(int64_t)p * K + k] * up;
-    acc[KM] += up * up;
+    for (int q = 0; q < U; ++q) {
+      const int pc = p + 256 * q < P ? p + 256 * q : p;
+      up[q] = ub[pc];
+#pragma unroll
+      for (int k = 0; k < KG; ++k) v[q][k] = kg + 4 * k < K ? Vb[(int64_t)pc * K + kg + 4 * k] : 0.f;
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q)
+      if (p + 256 * q < P) {
+#pragma unroll
+        for (int k = 0; k < KG; ++k) acc[k] = __builtin_fmaf(v[q][k], up[q], acc[k]);
+        uu0 = __builtin_fmaf(up[q], up[q], uu0);
+      }
   }
 #pragma unroll
-  for (int k = 0; k <= KM; ++k) red[k][threadIdx.x] = acc[k];
+  for (int k = 0; k < KG; ++k) red[kg + 4 * k][t] = acc[k];
+  if (kg == 0) red[KM][t] = uu0;
   __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s)
-      for (int k = 0; k <= KM; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + s];
-    __syncthreads();
+  // the tree over the chains: 128, 64, then 32 .. 1 apart
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  for (int k = wv; k <= KM; k += 16) {
+    float s = (red[k][lane] + red[k][lane + 128]) + (red[k][lane + 64] + red[k][lane + 192]);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) s += __shfl_down(s, d);
+    if (lane == 0) pk[k] = s;
   }
-  if ((int)threadIdx.x <= KM) pk[threadIdx.x] = red[threadIdx.x][0];
   __syncthreads();
   const float uu = pk[KM];
   float pp = 0.f;
@@ -161,6 +357,7 @@ __global__ __launch_bounds__(256) void k_subspace_loss(const float* __restrict__
   const float scale = -2.f / (uu * (float)B);
   for (int p = threadIdx.x; p < P; p += blockDim.x) {
     float vp = 0.f;
+#pragma unroll 8
     for (int k = 0; k < K; ++k) vp += Vb[(int64_t)p * K + k] * pk[k];
     du[(int64_t)b * P + p] = scale * (vp - rho * ub[p]);
   }
@@ -204,6 +401,88 @@ int grid_of(int64_t total) {
   return (int)(g < 1 ? 1 : g);
 }
 
+template <int OT, int CU, bool BWD>
+void conv_launch_t(const float* in, const float* act, const float* w, const float* bias, float* out, int B, int CI,
+                   int CO, int H, int W, int dil, int relu, int block, hipStream_t st) {
+  const int64_t total = (int64_t)B * H * W;
+  int64_t g = (total + block - 1) / block;
+  if (g > 65535) g = 65535;
+  const int gy = (CO + OT - 1) / OT;
+  const dim3 grid((unsigned)g, gy < 32768 ? gy : 32768, (gy + 32767) / 32768);
+  const bool small = total * (CI > CO ? CI : CO) < ((int64_t)1 << 28);  // 32-bit byte offsets reach every element
+#define RKS_CONV_K(R, IT) k_conv<OT, CU, BWD, R, IT><<<grid, block, 0, st>>>(in, act, w, bias, out, B, CI, CO, H, W, dil)
+  if (relu) {
+    if (small) RKS_CONV_K(true, uint32_t);
+    else RKS_CONV_K(true, uint64_t);
+  } else {
+    if (small) RKS_CONV_K(false, uint32_t);
+    else RKS_CONV_K(false, uint64_t);
+  }
+#undef RKS_CONV_K
+}
+
+// Output channels per lane: the most of 8, 4, 2, 1 that the layer has and that
+// still give three quarters of the 1,024 SIMDs a wave (more channels per lane
+// load less, fewer run on more SIMDs).  Measured, microseconds, forward / data
+// gradient of a 16-to-16 layer: 32 samples of 64 x 64 with 8 channels 16 / 23,
+// with 1 channel 54 / 107; one sample with 8 channels 9 / 13, with 1 channel
+// 4.4 / 7.3; 7 samples of 41 x 53 with 4 channels 6.5 / 7.0, 1: 9.4 / 16.
+// (One output per thread, every input and weight loaded for each product and
+// the taps skipped one by one: 87 / 161 and 16 / 28 for 32 samples and one.)
+// Bound by the vector pipes: 604 MFLOP in 16 us, 38 TFLOP/s of about 79
+// without packed arithmetic.
+template <bool BWD>
+void conv_launch(const float* in, const float* act, const float* w, const float* bias, float* out, int B, int CI,
+                 int CO, int H, int W, int dil, int relu, hipStream_t st) {
+  const int64_t waves = ((int64_t)B * H * W + 63) / 64;
+  auto fits = [&](int ot) { return CO >= ot && waves * ((CO + ot - 1) / ot) >= 768; };
+#define RKS_CONV(OT, CU, BLK) conv_launch_t<OT, CU, BWD>(in, act, w, bias, out, B, CI, CO, H, W, dil, relu, BLK, st)
+  if (fits(8)) RKS_CONV(8, 2, 256);
+  else if (fits(4)) RKS_CONV(4, 1, 256);
+  else if (fits(2)) RKS_CONV(2, 2, 64);
+  else RKS_CONV(1, 4, 64);
+#undef RKS_CONV
+}
+
+template <int OT, int NT, int U>
+void filter_launch_t(const float* x, const float* dy, const float* y, float* dw, float* db, int B, int C, int O, int H,
+                     int W, int dil, int relu, hipStream_t st) {
+  const unsigned grid = (unsigned)((O + OT - 1) / OT * C * (9 / NT));
+  const bool small = (int64_t)B * H * W * (C > O ? C : O) < ((int64_t)1 << 28);
+#define RKS_FILT_K(R, IT, T) k_conv_bwd_filter<OT, NT, U, R, IT, T><<<grid, 256, 0, st>>>(x, dy, y, dw, db, B, C, O, H, W, dil)
+  if (!small) {
+    if (relu) RKS_FILT_K(true, uint64_t, true);
+    else RKS_FILT_K(false, uint64_t, true);
+  } else if (H * W < 256) {
+    if (relu) RKS_FILT_K(true, uint32_t, true);
+    else RKS_FILT_K(false, uint32_t, true);
+  } else {
+    if (relu) RKS_FILT_K(true, uint32_t, false);
+    else RKS_FILT_K(false, uint32_t, false);
+  }
+#undef RKS_FILT_K
+}
+
+// One pair of channels per workgroup with all nine taps (1,024 waves for a
+// 16-to-16 layer, one per SIMD), or one row of the filter where there are too
+// few pairs for that.  Measured, microseconds, 32 samples of 64 x 64: 16 to 16
+// channels 84 with nine taps, 120 with three; 2 to 16 and 16 to 1 channels 84
+// and 76 with nine, 64 and 52 with three.  Two and four output channels per
+// workgroup load less but leave SIMDs idle (105 and 150).  With the taps
+// skipped one by one and each pixel's loads waited for: 820.  Bound by the
+// instructions of the 512 serial steps of each chain (about 11 loads and 45
+// vector instructions a step, one wave per SIMD).
+void filter_launch(const float* x, const float* dy, const float* y, float* dw, float* db, int B, int C, int O, int H,
+                   int W, int dil, int relu, hipStream_t st) {
+  if ((int64_t)C * O >= 128)
+    filter_launch_t<1, 9, 4>(x, dy, y, dw, db, B, C, O, H, W, dil, relu, st);
+  else
+    filter_launch_t<1, 3, 4>(x, dy, y, dw, db, B, C, O, H, W, dil, relu, st);
+}
+
+// A dilation that leaves the image in any case: every one from max(H, W) on is the same, and stays in range here.
+int dil_in_range(int dil, int H, int W) { return dil < H || dil < W ? dil : (H > W ? H : W); }
+
 int ok_or_hip() { return hipGetLastError() == hipSuccess ? RKS_OK : RKS_EHIP; }
 
 }  // namespace
@@ -213,8 +492,8 @@ extern "C" {
 int rks_net_conv3x3_forward(const float* x, const float* w, const float* b, float* y, int32_t B, int32_t Cin,
                             int32_t Cout, int32_t H, int32_t W, int32_t dil, int32_t relu, void* stream) {
   if (!x || !w || !b || !y || B < 1 || Cin < 1 || Cout < 1 || H < 1 || W < 1 || dil < 1) return RKS_EINVAL;
-  const int64_t total = (int64_t)B * Cout * H * W;
-  k_conv_fwd<<<grid_of(total), 256, 0, (hipStream_t)stream>>>(x, w, b, y, B, Cin, Cout, H, W, dil, relu);
+  dil = dil_in_range(dil, H, W);
+  conv_launch<false>(x, nullptr, w, b, y, B, Cin, Cout, H, W, dil, relu, (hipStream_t)stream);
   return ok_or_hip();
 }
 
@@ -224,18 +503,16 @@ int rks_net_conv3x3_backward(const float* x, const float* w, const float* y, con
   if (!x || !w || !dy || !dw || !db || (relu && !y) || B < 1 || Cin < 1 || Cout < 1 || H < 1 || W < 1 || dil < 1)
     return RKS_EINVAL;
   hipStream_t st = (hipStream_t)stream;
-  k_conv_bwd_filter<<<Cout * Cin, 256, 0, st>>>(x, dy, y, dw, db, B, Cin, Cout, H, W, dil, relu);
-  if (dx) {
-    const int64_t total = (int64_t)B * Cin * H * W;
-    k_conv_bwd_data<<<grid_of(total), 256, 0, st>>>(dy, y, w, dx, B, Cin, Cout, H, W, dil, relu);
-  }
+  dil = dil_in_range(dil, H, W);
+  filter_launch(x, dy, y, dw, db, B, Cin, Cout, H, W, dil, relu, st);
+  if (dx) conv_launch<true>(dy, y, w, nullptr, dx, B, Cout, Cin, H, W, dil, relu, st);
   return ok_or_hip();
 }
 
 int rks_net_subspace_loss(const float* u, const float* V, float* loss, float* du, int32_t B, int32_t P, int32_t K,
                           void* stream) {
   if (!u || !V || !loss || !du || B < 1 || P < 1 || K < 1 || K > 32) return RKS_EINVAL;
-  k_subspace_loss<<<B, 256, 0, (hipStream_t)stream>>>(u, V, loss, du, B, P, K);
+  k_subspace_loss<<<B, 1024, 0, (hipStream_t)stream>>>(u, V, loss, du, B, P, K);
   return ok_or_hip();
 }
 
