@@ -48,8 +48,11 @@ typedef enum { RKS_LM = 0, RKS_SM = 1, RKS_LR = 2, RKS_SR = 3 } rks_which;
  *  GAUSS  -- dense, entries N(0, 1/d);
  *  SPARSE -- zeta nonzeros +-1/sqrt(zeta) per column in distinct rows
  *            (Section 5 uses zeta = 8).
- * Omega is never stored: its entries are regenerated from Philox4x32-10
- * counters (column index, slot) keyed by sketch_seed. */
+ * Omega's entries are a function of Philox4x32-10 counters (column index,
+ * slot) keyed by sketch_seed.  A sparse Omega is regenerated by every kernel
+ * that needs it; a context stores a Gaussian one of up to 4 GiB (8 n d bytes)
+ * and regenerates a larger one, or one the device has no room for, with the
+ * same results to the bit. */
 typedef enum { RKS_SKETCH_GAUSS = 0, RKS_SKETCH_SPARSE = 1 } rks_sketch_kind;
 
 /* Storage precision of the n-dimensional basis U (mixed precision is the
@@ -236,7 +239,8 @@ typedef struct {
  * rotation writes at most 128 columns), tol > 0, a valid CSR.  opts may be
  * NULL (defaults).
  * Allocates the basis U (n x (m+1)), the sketch S (d x (m+1)), the Rayleigh
- * quotient B ((m+1) x m) and scratch on the device.
+ * quotient B ((m+1) x m) and scratch on the device, and a Gaussian Omega of
+ * up to 4 GiB.
  * Errors: RKS_EINVAL, RKS_ENAN (non-finite value in A), RKS_ENOMEM, RKS_EHIP. */
 int rks_create(const rks_csr* A, int32_t k, int32_t m, int32_t d, int32_t which, double tol,
                const rks_opts* opts, struct rks_ctx** out);

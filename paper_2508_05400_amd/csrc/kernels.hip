@@ -1627,12 +1627,23 @@ inline int grid_for(int64_t work, int per_block, int cap) {
 // evaluated once, by a different lane than its neighbours in the sum, and
 // nothing is accumulated atomically.  The waves' sums are added in a fixed
 // order; row bx of part gets this block's bins.
+// A second vector y (HY; x is optional then, HX) is sketched by the same
+// evaluation of the pairs, into rows of its own.  OM: the pairs are read from
+// the context's stored Omega (om; the same values, so the same sums to the
+// bit) instead of evaluated: a pair costs ten Philox rounds and an FP64
+// logarithm, root, sine and cosine, some 2,000 cycles for a wave's 1 KB of
+// Omega, 1.3 TB/s at best, where a read runs at the rate of the memory.
+// Measured on n = 10,000, d = 80, an Arnoldi step's two sketches: 23.2 us
+// evaluated one after the other, 4.1 us read together (6.4 MB, from the L2s).
 constexpr int kGsMinRows = 32;
+constexpr int kGsU = 8;  // rows of Omega in flight
 
-template <typename TX>
-__global__ __launch_bounds__(256) void k_gauss_sketch(int64_t n, const TX* __restrict__ x, int64_t R,
-                                                      double* __restrict__ part, SketchP sp) {
-  __shared__ double acc[4][2][64];
+template <typename TX, typename TY, bool HX, bool HY, bool OM>
+__global__ __launch_bounds__(256) void k_gauss_sketch(int64_t n, const TX* __restrict__ x, const TY* __restrict__ y,
+                                                      int64_t R, double* __restrict__ part,
+                                                      double* __restrict__ party, SketchP sp,
+                                                      const double* __restrict__ om) {
+  __shared__ double acc[4][2][64], accy[HY ? 4 : 1][2][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int np = (sp.d + 1) >> 1;
   const int p = (int)blockIdx.y * 64 + lane;
@@ -1640,30 +1651,76 @@ __global__ __launch_bounds__(256) void k_gauss_sketch(int64_t n, const TX* __res
   const int64_t rend = min(n, r0 + R);
   const int64_t Rw = (R + 3) >> 2;
   const int64_t a0 = min(rend, r0 + wv * Rw), a1 = min(rend, a0 + Rw);
-  double s0 = 0.0, s1 = 0.0;
+  double s0 = 0.0, s1 = 0.0, t0 = 0.0, t1 = 0.0;
   for (int64_t c = a0; c < a1; c += 64) {  // wave-uniform trip count
     const int64_t i = c + lane;
-    const double xv = i < a1 ? Conv<TX>::ld(x[i]) : 0.0;
+    const double xv = HX && i < a1 ? Conv<TX>::ld(x[i]) : 0.0;
+    const double yv = HY && i < a1 ? Conv<TY>::ld(y[i]) : 0.0;
     const int cnt = (int)min((int64_t)64, a1 - c);
-    for (int j = 0; j < cnt; ++j) {
-      const double v = readlane_f64(xv, j);
-      if (p < np) {
-        double g0, g1;
-        gauss_pair((uint64_t)(c + j), (uint32_t)p, 0u, sp.k0, sp.k1, g0, g1);
+    auto add = [&](int j, double g0, double g1) {
+      if (HX) {
+        const double v = readlane_f64(xv, j);
         s0 += g0 * v;
         s1 += g1 * v;
       }
+      if (HY) {
+        const double u = readlane_f64(yv, j);
+        t0 += g0 * u;
+        t1 += g1 * u;
+      }
+    };
+    if constexpr (OM) {
+      typedef double d2v __attribute__((ext_vector_type(2)));
+      const d2v* col = (const d2v*)om + c * np + (p < np ? p : np - 1);
+      for (int j0 = 0; j0 < cnt; j0 += kGsU) {
+        d2v g[kGsU];
+#pragma unroll
+        for (int j = 0; j < kGsU; ++j) g[j] = col[(int64_t)(j0 + j < cnt ? j0 + j : j0) * np];
+#pragma unroll
+        for (int j = 0; j < kGsU; ++j)
+          if (j0 + j < cnt) add(j0 + j, g[j].x, g[j].y);
+      }
+    } else {
+      for (int j = 0; j < cnt; ++j)
+        if (p < np) {
+          double g0, g1;
+          gauss_pair((uint64_t)(c + j), (uint32_t)p, 0u, sp.k0, sp.k1, g0, g1);
+          add(j, g0, g1);
+        }
     }
   }
-  acc[wv][0][lane] = s0;
-  acc[wv][1][lane] = s1;
+  if (HX) {
+    acc[wv][0][lane] = s0;
+    acc[wv][1][lane] = s1;
+  }
+  if (HY) {
+    accy[HY ? wv : 0][0][lane] = t0;
+    accy[HY ? wv : 0][1][lane] = t1;
+  }
   __syncthreads();
+  auto put = [&](const double (*a)[2][64], double* out) {
+    const double q0 = ((a[0][0][lane] + a[1][0][lane]) + a[2][0][lane]) + a[3][0][lane];
+    const double q1 = ((a[0][1][lane] + a[1][1][lane]) + a[2][1][lane]) + a[3][1][lane];
+    double* row = out + (size_t)blockIdx.x * sp.d;
+    row[2 * p] = q0 * sp.scale;
+    if (2 * p + 1 < sp.d) row[2 * p + 1] = q1 * sp.scale;
+  };
   if (wv == 0 && p < np) {
-    const double t0 = ((acc[0][0][lane] + acc[1][0][lane]) + acc[2][0][lane]) + acc[3][0][lane];
-    const double t1 = ((acc[0][1][lane] + acc[1][1][lane]) + acc[2][1][lane]) + acc[3][1][lane];
-    double* row = part + (size_t)blockIdx.x * sp.d;
-    row[2 * p] = t0 * sp.scale;
-    if (2 * p + 1 < sp.d) row[2 * p + 1] = t1 * sp.scale;
+    if constexpr (HX) put(acc, part);
+    if constexpr (HY) put(accy, party);
+  }
+}
+
+// The stored Gaussian embedding of a context (LaunchEnv::om): the pairs of
+// column i at 2 (np i), np = (d + 1) / 2.
+__global__ __launch_bounds__(256) void k_omega_fill(int64_t n, double* __restrict__ om, SketchP sp) {
+  const int64_t np = (sp.d + 1) >> 1, total = n * np;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += stride) {
+    double g0, g1;
+    gauss_pair((uint64_t)(e / np), (uint32_t)(e % np), 0u, sp.k0, sp.k1, g0, g1);
+    om[2 * e] = g0;
+    om[2 * e + 1] = g1;
   }
 }
 
@@ -1717,17 +1774,47 @@ static void launch_k(const LaunchEnv& e, bool first, bool last, void (*k)(KArgs.
     k<<<grid, block, lds, e.stream>>>(static_cast<KArgs>(args)...);
 }
 
-// The Gaussian sketch of x (n entries of type TX) as partial rows of part;
-// returns the number of rows (<= kMaxG).
-template <typename TX>
-static int gauss_t(const LaunchEnv& e, const TX* x, double* part) {
+// The Gaussian sketches of x and y (n entries; either may be null) as partial
+// rows of px and py; returns the number of rows (<= kMaxG).
+template <typename TX, typename TY, bool HX, bool HY>
+static int gauss_xy_t(const LaunchEnv& e, bool first, const TX* x, const TY* y, double* px, double* py) {
   const int np = (e.sp.d + 1) >> 1;
   int64_t R = (e.n + kMaxG - 1) / kMaxG;
   if (R < kGsMinRows) R = kGsMinRows;
   const int Gx = (int)((e.n + R - 1) / R);
   dim3 grid(Gx, (np + 63) / 64), block(256);
-  launch_k(e, false, true, k_gauss_sketch<TX>, grid, block, 0, e.n, x, R, part, e.sp);
+  if (e.om)
+    launch_k(e, first, true, k_gauss_sketch<TX, TY, HX, HY, true>, grid, block, 0, e.n, x, y, R, px, py, e.sp, e.om);
+  else
+    launch_k(e, first, true, k_gauss_sketch<TX, TY, HX, HY, false>, grid, block, 0, e.n, x, y, R, px, py, e.sp,
+             nullptr);
   return Gx;
+}
+
+template <typename TX, typename TY>
+static int gauss_xy(const LaunchEnv& e, const TX* x, const TY* y, double* px, double* py) {
+  if (x && y) return gauss_xy_t<TX, TY, true, true>(e, true, x, y, px, py);
+  if (x) return gauss_xy_t<TX, TX, true, false>(e, true, x, nullptr, px, nullptr);
+  return gauss_xy_t<TY, TY, true, false>(e, true, y, nullptr, py, nullptr);
+}
+
+// The sketch of one vector as the last kernel of a launcher.
+template <typename TX>
+static int gauss_t(const LaunchEnv& e, const TX* x, double* part) {
+  return gauss_xy_t<TX, TX, true, false>(e, false, x, nullptr, part, nullptr);
+}
+
+// A producer's own Gaussian sketch of what it wrote, unless the caller takes it with launch_gauss.
+static bool gauss_here(const LaunchEnv& e) { return e.sp_kind == 0 && !e.gauss_apart; }
+
+int launch_gauss(const LaunchEnv& e, const void* w, const void* u, double* pw, double* pu) {
+  if (e.prec == 1) return gauss_xy(e, (const float*)w, (const float*)u, pw, pu);
+  if (e.prec == 2) return gauss_xy(e, (const float*)w, (const bf16_t*)u, pw, pu);
+  return gauss_xy(e, (const double*)w, (const double*)(e.prec == 3 && u ? e.xcur : u), pw, pu);
+}
+
+void launch_omega_fill(const LaunchEnv& e, double* om) {
+  k_omega_fill<<<grid_for(e.n * ((e.sp.d + 1) / 2), 256, 4096), 256, 0, e.stream>>>(e.n, om, e.sp);
 }
 
 template <typename TV, typename TW, typename TA>
@@ -1737,10 +1824,10 @@ static int spmv_panel_t(const LaunchEnv& e, const TA* val, const TV* x, TW* w, d
   const size_t bins = bins_lds(e, kSpmvWaves, do_sketch && e.sp_kind == 1);
   const size_t lds = accn * 8 + (stage > bins ? stage : bins);
   RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_spmv_panel<TV, TW, TA, KIND>, lds);
-                    launch_k(e, true, !(do_sketch && e.sp_kind == 0), k_spmv_panel<TV, TW, TA, KIND>,
+                    launch_k(e, true, !(do_sketch && gauss_here(e)), k_spmv_panel<TV, TW, TA, KIND>,
                              dim3(e.npanels), dim3(64 * kSpmvWaves), lds, e.n, e.rows_pp, e.col_pn, val,
                              (const int4*)e.tiles_pn, e.toff_pn, e.off_pn, e.ptile, x, w, zpart, e.sp, do_sketch));
-  if (do_sketch && e.sp_kind == 0) return gauss_t<TW>(e, w, zpart);
+  if (do_sketch && gauss_here(e)) return gauss_t<TW>(e, w, zpart);
   return e.npanels;
 }
 
@@ -1750,10 +1837,10 @@ static int spmv_sell_t(const LaunchEnv& e, const TS* val, const TV* x, TW* w, do
   if (G >= 8) G &= ~7;  // a multiple of the XCD count (see the slice mapping)
   const size_t lds = bins_lds(e, kSpmvWaves, do_sketch && e.sp_kind == 1);
   RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_spmv_sell<TV, TW, TA, KIND, TS>, lds);
-                    launch_k(e, true, !(do_sketch && e.sp_kind == 0), k_spmv_sell<TV, TW, TA, KIND, TS>, dim3(G),
+                    launch_k(e, true, !(do_sketch && gauss_here(e)), k_spmv_sell<TV, TW, TA, KIND, TS>, dim3(G),
                              dim3(64 * kSpmvWaves), lds, e.rp, e.sl_off, e.nsl, e.col_sl, val, e.vtab, e.n, x, w,
                              zpart, e.sp, do_sketch, e.sl_pad0));
-  if (do_sketch && e.sp_kind == 0) return gauss_t<TW>(e, w, zpart);
+  if (do_sketch && gauss_here(e)) return gauss_t<TW>(e, w, zpart);
   return G;
 }
 
@@ -1778,26 +1865,26 @@ int launch_spmv_sketch(const LaunchEnv& e, const void* x, void* w, double* zpart
   const size_t lds = bins_lds(e, kSpmvWaves, do_sketch && e.sp_kind == 1);
   if (prec == 0 && e.vidx) {  // value-indexed FP64 product
     RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_spmv_sketch<double, double, double, KIND, uint8_t>, lds);
-                      launch_k(e, true, !(do_sketch && e.sp_kind == 0), k_spmv_sketch<double, double, double, KIND, uint8_t>,
+                      launch_k(e, true, !(do_sketch && gauss_here(e)), k_spmv_sketch<double, double, double, KIND, uint8_t>,
                                grid, block, lds, e.rp, e.col, e.vidx, e.vtab, (const int4*)e.tiles, e.ntiles,
                                (const double*)x, (double*)w, zpart, e.sp, do_sketch));
   } else if (prec == 0) {
     RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_spmv_sketch<double, double, double, KIND>, lds);
-                      launch_k(e, true, !(do_sketch && e.sp_kind == 0), k_spmv_sketch<double, double, double, KIND>, grid, block, lds,
+                      launch_k(e, true, !(do_sketch && gauss_here(e)), k_spmv_sketch<double, double, double, KIND>, grid, block, lds,
                                e.rp, e.col, e.val, nullptr, (const int4*)e.tiles, e.ntiles, (const double*)x, (double*)w,
                                zpart, e.sp, do_sketch));
   } else if (prec == 1) {
     RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_spmv_sketch<float, float, float, KIND>, lds);
-                      launch_k(e, true, !(do_sketch && e.sp_kind == 0), k_spmv_sketch<float, float, float, KIND>, grid, block, lds,
+                      launch_k(e, true, !(do_sketch && gauss_here(e)), k_spmv_sketch<float, float, float, KIND>, grid, block, lds,
                                e.rp, e.col, e.val32, nullptr, (const int4*)e.tiles, e.ntiles, (const float*)x, (float*)w,
                                zpart, e.sp, do_sketch));
   } else {
     RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_spmv_sketch<bf16_t, float, float, KIND>, lds);
-                      launch_k(e, true, !(do_sketch && e.sp_kind == 0), k_spmv_sketch<bf16_t, float, float, KIND>, grid, block, lds,
+                      launch_k(e, true, !(do_sketch && gauss_here(e)), k_spmv_sketch<bf16_t, float, float, KIND>, grid, block, lds,
                                e.rp, e.col, e.val32, nullptr, (const int4*)e.tiles, e.ntiles, (const bf16_t*)x, (float*)w,
                                zpart, e.sp, do_sketch));
   }
-  if (do_sketch && e.sp_kind == 0)
+  if (do_sketch && gauss_here(e))
     return prec == 0 ? gauss_t<double>(e, (const double*)w, zpart) : gauss_t<float>(e, (const float*)w, zpart);
   return G;
 }
@@ -1861,7 +1948,7 @@ static void ls_update_t(const LaunchEnv& e, dim3 grid, size_t lds, int t, int pe
   int16_t* unew_lo = SPLIT ? e.lo_of(unew) : nullptr;
   double* xout = SPLIT ? e.xcur : nullptr;
   RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_ls_update<TV, TW, KIND, PRE, PB, ROLL, SPLIT>, lds);
-                    launch_k(e, true, e.sp_kind != 0, k_ls_update<TV, TW, KIND, PRE, PB, ROLL, SPLIT>, grid, dim3(1024),
+                    launch_k(e, true, !gauss_here(e), k_ls_update<TV, TW, KIND, PRE, PB, ROLL, SPLIT>, grid, dim3(1024),
                              lds, t, e.sp.d, pending, zraw, sraw, S, B, ldb, E, cs, coef, scal, flags, bd_rel, e.n,
                              npk, (const TV*)U, ldu, (const TW*)w, (TV*)unew, spart, e.sp, Ulo, unew_lo, xout));
 }
@@ -1906,7 +1993,7 @@ int launch_ls_update(const LaunchEnv& e, int t, int pending, const double* zraw,
   else RKS_LSU(float, double, true);
 #undef RKS_LSU
 #undef RKS_LSU_PB
-  if (e.sp_kind == 0) {  // sketch of the stored value (the pair basis: of its FP64 copy)
+  if (gauss_here(e)) {  // sketch of the stored value (the pair basis: of its FP64 copy)
     if (e.prec == 0) return gauss_t<double>(e, (const double*)unew, spart);
     if (e.prec == 1) return gauss_t<float>(e, (const float*)unew, spart);
     if (e.prec == 2) return gauss_t<bf16_t>(e, (const bf16_t*)unew, spart);
@@ -1939,7 +2026,7 @@ int launch_init(const LaunchEnv& e, void* u, const double* u0, uint32_t s0, uint
                           e.n, (float*)u, u0, s0, s1, c2, tag, spart, e.sp, store, store ? e.lo_of(u) : nullptr,
                           e.xcur));
   }
-  if (e.sp_kind == 0) {
+  if (e.sp_kind == 0 && !(store && e.gauss_apart)) {
     // sketch of the stored value; without a store, of u0 itself (FP64 only)
     if (!store) return u0 ? gauss_t<double>(e, u0, spart) : 0;
     if (prec == 0) return gauss_t<double>(e, (const double*)u, spart);

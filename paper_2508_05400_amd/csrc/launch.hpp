@@ -26,6 +26,12 @@ struct LaunchEnv {
   int64_t ldu;         // basis leading dimension (n rounded up to 128; padding rows are zero)
   int sp_kind;         // 0 Gaussian (applied by k_gauss_sketch), 1 sparse-sign, 2 none (deterministic KS)
   SketchP sp;
+  // Gaussian Omega (sp_kind 0) of a context: its unscaled entries, column
+  // after column, d rounded up to even of each, or null to generate them; gauss_apart:
+  // the producers do not sketch what they write, launch_gauss does it for two
+  // of them together
+  const double* om = nullptr;
+  int gauss_apart = 0;
   // column-blocked SpMV (used when cb = 1): the layout of panels.hpp, one
   // workgroup per row panel of rows_pp rows
   int cb = 0;
@@ -71,6 +77,13 @@ struct LaunchEnv {
 // kMaxPart for the row tiles, npanels for the column-blocked layout).  For the
 // pair basis (prec 3) x and w are FP64.
 int launch_spmv_sketch(const LaunchEnv& e, const void* x, void* w, double* zpart, int do_sketch, int prec_override);
+// Partials of Omega w (w as launch_spmv_sketch writes it for the basis, to
+// pw) and of Omega u (u a basis column; the pair basis: its FP64 copy xcur;
+// to pu) for a Gaussian Omega; either of w and u may be null.  Returns the
+// number of partial rows (at most kMaxG) of each.
+int launch_gauss(const LaunchEnv& e, const void* w, const void* u, double* pw, double* pu);
+// Fills LaunchEnv::om.
+void launch_omega_fill(const LaunchEnv& e, double* om);
 void launch_reduce(const LaunchEnv& e, const double* pa, int Ga, const double* pb, int Gb, double* oa, double* ob);
 // E = S^T S - I ((m+1) x (m+1), leading dimension ldb), kept current column by column.
 void launch_ls(const LaunchEnv& e, int t, int pending, int finalize_only, const double* zraw, const double* sraw,

@@ -1,4 +1,4 @@
-// Device-side counter-based random numbers for the never-stored embedding.
+// Device-side counter-based random numbers of the embedding and the start vectors.
 //
 // Philox4x32-10 (Salmon et al., SC'11): 4x32-bit counter, 2x32-bit key,
 // ten rounds, Weyl key schedule.  Stream layout (key = seed split in two

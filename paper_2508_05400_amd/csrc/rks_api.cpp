@@ -87,6 +87,7 @@ struct rks_ctx {
   double *S = nullptr, *B = nullptr, *cs = nullptr, *coef = nullptr, *z = nullptr, *sr = nullptr;
   double *zpart = nullptr, *spart = nullptr, *scal = nullptr, *Yd = nullptr, *u0tmp = nullptr;
   double* E = nullptr;  // S^T S - I, (m+1) x (m+1), leading dimension m+1
+  double* om = nullptr;     // stored Gaussian Omega (null: generated by each sketch)
   double* kpart = nullptr;  // deterministic Krylov-Schur: partial rows of U^T x (kMaxG x (m+1))
   bool ks = false;          // deterministic Krylov-Schur (RKS_METHOD_KS_CGS2)
   // column-blocked SpMV layout (when chosen): A by row panel and column block, its tiles
@@ -259,6 +260,9 @@ int arnoldi_step(rks_ctx* c, int t) {
     ProfK p(c, CAT_SPMV, timed, e);
     c->G_z = rks::launch_spmv_sketch(p.env, spmv_x(c, t), c->w, c->zpart, 1, spmv_prec(c));
   }
+  // a Gaussian Omega: of w and of the pending column in one pass over its entries
+  if (e.sp_kind == 0)
+    c->G_z = c->G_s = rks::launch_gauss(e, c->w, c->pending ? basis_col(c, t) : nullptr, c->zpart, c->spart);
   {
     ProfK p(c, CAT_REDUCE, timed, e);
     rks::launch_reduce(p.env, c->zpart, c->G_z, c->pending ? c->spart : nullptr, c->G_s, c->z, c->sr);
@@ -356,6 +360,7 @@ int arnoldi_step_ks(rks_ctx* c, int t) {
 
 int finalize_last(rks_ctx* c) {
   const auto& e = *c->lenv;
+  if (e.sp_kind == 0) c->G_s = rks::launch_gauss(e, nullptr, basis_col(c, c->j), nullptr, c->spart);
   rks::launch_reduce(e, nullptr, 0, c->spart, c->G_s, c->z, c->sr);
   rks::launch_ls(e, c->j, 1, 1, c->z, c->sr, c->S, c->B, c->m + 1, c->E, c->cs, c->coef, c->scal, c->flags,
                  kBreakdownRel);
@@ -482,8 +487,9 @@ int recover_breakdown(rks_ctx* c, int t) {
   const uint64_t s = c->o.start_seed;
   // w is FP64 (FP64 and pair bases), or FP32 with an FP32 or BF16 basis
   const int wprec = c->wbytes == 8 ? 0 : 1;
-  const int G = rks::launch_init(e, c->w, nullptr, (uint32_t)s, (uint32_t)(s >> 32), c->zpart, 1, wprec,
-                                 (uint32_t)c->breakdowns, 3u);
+  int G = rks::launch_init(e, c->w, nullptr, (uint32_t)s, (uint32_t)(s >> 32), c->zpart, 1, wprec,
+                           (uint32_t)c->breakdowns, 3u);
+  if (e.sp_kind == 0) G = rks::launch_gauss(e, c->w, nullptr, c->zpart, nullptr);
   rks::launch_reduce(e, c->zpart, G, nullptr, 0, c->z, nullptr);
   c->G_s = rks::launch_ls_update(e, t - 1, 0, c->z, c->sr, c->S, c->B, ldb, c->E, c->cs, c->coef, c->scal,
                                  c->flags, kBreakdownRel, c->U, c->ldu, c->w, basis_col(c, t), c->spart);
@@ -1058,7 +1064,7 @@ bool valid_csr(const int32_t* rp, const int32_t* col, int64_t n, int64_t nnz, st
 
 void free_all(rks_ctx* c) {
   void* dev[] = {c->rp, c->col, c->tiles, c->dstate, c->val, c->val32, c->U_lo, c->U64, c->w, c->xcur,
-                 c->coef, c->z, c->sr, c->zpart, c->spart, c->scal, c->Yd, c->u0tmp, c->kpart,
+                 c->coef, c->z, c->sr, c->zpart, c->spart, c->scal, c->Yd, c->u0tmp, c->kpart, c->om,
                  c->col_pn, c->tiles_pn, c->toff_pn, c->ptile, c->off_pn, c->val_pn, c->val32_pn,
                  c->Xr, c->ax1, c->ax2, c->rpart, c->vidx, c->vtab, c->sl_off, c->col_sl, c->val_sl,
                  c->vidx_sl, c->val32_sl};
@@ -1473,6 +1479,19 @@ int rks_create(const rks_csr* A, int32_t k, int32_t m, int32_t d, int32_t which,
     e.sp.d = 1;
     e.sp.scale = 1.0;
   }
+  if (!c->ks && o.sketch_kind == RKS_SKETCH_GAUSS) {
+    e.gauss_apart = 1;
+    const size_t bytes = (size_t)((d + 1) / 2) * n * 16;
+    if (bytes <= rks::kOmegaMax) {
+      if (hipMalloc((void**)&c->om, bytes) == hipSuccess) {
+        rks::launch_omega_fill(e, c->om);
+        e.om = c->om;
+      } else {  // generated by each sketch instead
+        c->om = nullptr;
+        (void)hipGetLastError();
+      }
+    }
+  }
   *out = c;
   return RKS_OK;
 }
@@ -1625,8 +1644,10 @@ int rks_sketch_noalloc(int64_t n, int32_t d, int32_t sketch_kind, int32_t zeta, 
 int rks_spmv_sketch(rks_ctx* c, const double* x_dev, double* w_dev, double* z_dev) {
   if (!c || !x_dev || !w_dev || !z_dev) return RKS_EINVAL;
   if (c->ks) return fail(c, RKS_EINVAL, "deterministic Krylov-Schur has no sketch");
-  const int G = rks::launch_spmv_sketch(c->env, x_dev, w_dev, c->zpart, 1, 0);
-  rks::launch_reduce(c->env, c->zpart, G, nullptr, 0, z_dev, nullptr);
+  rks::LaunchEnv e = c->env;
+  e.gauss_apart = 0;
+  const int G = rks::launch_spmv_sketch(e, x_dev, w_dev, c->zpart, 1, 0);
+  rks::launch_reduce(e, c->zpart, G, nullptr, 0, z_dev, nullptr);
   HIPCHK(c, hipGetLastError());
   HIPCHK(c, hipStreamSynchronize(c->env.stream));
   return RKS_OK;
