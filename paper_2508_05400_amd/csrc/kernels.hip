@@ -1008,9 +1008,16 @@ struct ColPk {
     RawL raw;
     int16_t v[SPLIT ? PB / 4 : 2];
   } l;
+  // KEEP: a plain load; otherwise non-temporal (see launch_ls_update)
+  template <bool KEEP = false>
   __device__ __forceinline__ void load(const TV* hi, const int16_t* lo, int64_t off) {
-    h.raw = __builtin_nontemporal_load((const Raw*)(hi + off));
-    if constexpr (SPLIT) l.raw = __builtin_nontemporal_load((const RawL*)(lo + off));
+    if constexpr (KEEP) {
+      h.raw = *(const Raw*)(hi + off);
+      if constexpr (SPLIT) l.raw = *(const RawL*)(lo + off);
+    } else {
+      h.raw = __builtin_nontemporal_load((const Raw*)(hi + off));
+      if constexpr (SPLIT) l.raw = __builtin_nontemporal_load((const RawL*)(lo + off));
+    }
   }
   __device__ __forceinline__ double val(int r) const {
     if constexpr (SPLIT) return pair_val(h.v[r], l.v[r]);
@@ -1029,8 +1036,9 @@ struct ColPk {
 // unew_lo), and the stored value of the new column also goes to xout in FP64
 // (the next product with A reads it there).
 // Each thread owns V consecutive rows and streams every basis column once
-// with one 16-byte non-temporal load per column, in groups of 8 (8 loads,
-// then their FMAs).  ROLL: a rolling window of 8 instead, where the slot of
+// with one 16-byte load per column (plain for the first nkeep columns, non-
+// temporal for the others, see kept_columns), in groups of 8 (8 loads, then
+// their FMAs).  ROLL: a rolling window of 8 instead, where the slot of
 // column l is refilled with column l + 8 as soon as it is consumed.  Measured:
 // the window pays in k_ls_update without its prefetch when each thread walks
 // 4 or more packets (one 16-wave workgroup per CU; 393 -> 364 us per launch
@@ -1047,7 +1055,8 @@ __device__ __forceinline__ void update_body(int64_t n, int64_t npk, int ncol, co
                                             TV* __restrict__ unew, double* __restrict__ spart, SketchP sp,
                                             double* bins, const typename RawOf<PB>::type* pre = nullptr,
                                             bool use_pre = false, const int16_t* __restrict__ Ulo = nullptr,
-                                            int16_t* __restrict__ unew_lo = nullptr, double* __restrict__ xout = nullptr) {
+                                            int16_t* __restrict__ unew_lo = nullptr, double* __restrict__ xout = nullptr,
+                                            int nkeep = 0) {
   // pre: NPRE leading basis columns, then (PREW) the w chunks, of the first packet
   typedef typename RawOf<PB>::type Raw;
   constexpr int V = PB / sizeof(TV);
@@ -1091,13 +1100,13 @@ __device__ __forceinline__ void update_body(int64_t n, int64_t npk, int ncol, co
       ColPk<TV, PB, SPLIT> p[8];
 #pragma unroll
       for (int q = 0; q < 8; ++q)
-        if (l + q < ncol) p[q].load(col0, col0l, (int64_t)(l + q) * ldu);
+        if (l + q < ncol) p[q].template load<false>(col0, col0l, (int64_t)(l + q) * ldu);
       for (; l < ncol; l += 8) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
           if (l + q < ncol) {
             const ColPk<TV, PB, SPLIT> cur = p[q];
-            if (l + q + 8 < ncol) p[q].load(col0, col0l, (int64_t)(l + q + 8) * ldu);
+            if (l + q + 8 < ncol) p[q].template load<false>(col0, col0l, (int64_t)(l + q + 8) * ldu);
             const double cq = coef[l + q];
 #pragma unroll
             for (int r = 0; r < V; ++r) a[r] -= cq * cur.val(r);
@@ -1105,20 +1114,23 @@ __device__ __forceinline__ void update_body(int64_t n, int64_t npk, int ncol, co
         }
       }
     } else {
-      for (; l + 8 <= ncol; l += 8) {
+      auto group = [&](auto keep) {
         ColPk<TV, PB, SPLIT> p[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) p[q].load(col0, col0l, (int64_t)(l + q) * ldu);
+        for (int q = 0; q < 8; ++q) p[q].template load<decltype(keep)::value>(col0, col0l, (int64_t)(l + q) * ldu);
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
           const double cq = coef[l + q];
 #pragma unroll
           for (int r = 0; r < V; ++r) a[r] -= cq * p[q].val(r);
         }
-      }
+      };
+      const int lk = min(nkeep, ncol);
+      for (; l + 8 <= lk; l += 8) group(std::true_type());
+      for (; l + 8 <= ncol; l += 8) group(std::false_type());
       for (; l < ncol; ++l) {
         ColPk<TV, PB, SPLIT> p;
-        p.load(col0, col0l, (int64_t)l * ldu);
+        p.template load<true>(col0, col0l, (int64_t)l * ldu);
         const double cq = coef[l];
 #pragma unroll
         for (int r = 0; r < V; ++r) a[r] -= cq * p.val(r);
@@ -1127,9 +1139,15 @@ __device__ __forceinline__ void update_body(int64_t n, int64_t npk, int ncol, co
     ColPk<TV, PB, SPLIT> o;
 #pragma unroll
     for (int r = 0; r < V; ++r) o.set(r, a[r]);
-    __builtin_nontemporal_store(o.h.raw, (Raw*)(unew + i0));
-    if constexpr (SPLIT)
-      __builtin_nontemporal_store(o.l.raw, (typename ColPk<TV, PB, SPLIT>::RawL*)(unew_lo + i0));
+    if (!ROLL && ncol < nkeep) {
+      *(Raw*)(unew + i0) = o.h.raw;
+      if constexpr (SPLIT) *(typename ColPk<TV, PB, SPLIT>::RawL*)(unew_lo + i0) = o.l.raw;
+      asm volatile("" ::: "memory");  // (keeps the compiler from merging the two branches into plain stores)
+    } else {
+      __builtin_nontemporal_store(o.h.raw, (Raw*)(unew + i0));
+      if constexpr (SPLIT)
+        __builtin_nontemporal_store(o.l.raw, (typename ColPk<TV, PB, SPLIT>::RawL*)(unew_lo + i0));
+    }
     if constexpr (SPLIT) {
       typedef double d2v __attribute__((ext_vector_type(2)));
 #pragma unroll
@@ -1156,9 +1174,10 @@ template <typename TV, typename TW, int KIND>
 __global__ __launch_bounds__(1024) void k_update(int64_t n, int64_t npk, int ncol, const TV* __restrict__ U,
                                                 int64_t ldu, const TW* __restrict__ w,
                                                 const double* __restrict__ coef, TV* __restrict__ unew,
-                                                double* __restrict__ spart, SketchP sp) {
+                                                double* __restrict__ spart, SketchP sp, int nkeep) {
   extern __shared__ double bins[];  // 16 waves x d (none for KIND 3)
-  update_body<TV, TW, KIND>(n, npk, ncol, U, ldu, w, coef, unew, spart, sp, bins);
+  update_body<TV, TW, KIND>(n, npk, ncol, U, ldu, w, coef, unew, spart, sp, bins, nullptr, false, nullptr, nullptr,
+                            nullptr, nkeep);
 }
 
 // One randomized Arnoldi step's least squares and update in one launch: every
@@ -1178,7 +1197,7 @@ __global__ __launch_bounds__(1024) void k_ls_update(int t, int d, int pending, c
                                                    const TW* __restrict__ w, TV* __restrict__ unew,
                                                    double* __restrict__ spart, SketchP sp,
                                                    const int16_t* __restrict__ Ulo, int16_t* __restrict__ unew_lo,
-                                                   double* __restrict__ xout) {
+                                                   double* __restrict__ xout, int nkeep) {
   extern __shared__ double smem[];
   double* hc = smem;
   double* work = smem + kMaxM + 2;
@@ -1204,13 +1223,14 @@ __global__ __launch_bounds__(1024) void k_ls_update(int t, int d, int pending, c
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
       const int qc = q <= t ? q : t;
-      pre[q] = __builtin_nontemporal_load((const Raw*)(U + gl * V + (int64_t)qc * ldu));
+      const Raw* src = (const Raw*)(U + gl * V + (int64_t)qc * ldu);
+      pre[q] = *src;
     }
 #pragma unroll
     for (int c = 0; c < (PREW ? WCH : 0); ++c) pre[NP + c] = *(const Raw*)(w + gl * V + c * (PB / sizeof(TW)));
   });
   update_body<TV, TW, KIND, NP, PREW, PB, ROLL && NP == 0, SPLIT>(n, npk, t + 1, U, ldu, w, hc, unew, spart, sp,
-                                                              work, pre, use_pre, Ulo, unew_lo, xout);
+                                                              work, pre, use_pre, Ulo, unew_lo, xout, nkeep);
 }
 
 // Sums over the wave of eight values per lane: lane L returns the total of
@@ -1242,7 +1262,8 @@ __device__ __forceinline__ double wave_sum8(const double v[8], int lane) {
 // eight with one wave_sum8 per group.
 template <typename TV, typename TX>
 __global__ __launch_bounds__(1024) void k_dots(int64_t n, int64_t npk, int ncol, const TV* __restrict__ U,
-                                               int64_t ldu, const TX* __restrict__ x, double* __restrict__ part) {
+                                               int64_t ldu, const TX* __restrict__ x, double* __restrict__ part,
+                                               int nkeep) {
   constexpr int V = 16 / sizeof(TV);
   __shared__ double bins[16][kMaxM + 8];  // one row per wave, added in wave order at the end
   for (int b = threadIdx.x; b < 16 * (kMaxM + 8); b += blockDim.x) bins[b / (kMaxM + 8)][b % (kMaxM + 8)] = 0.0;
@@ -1257,22 +1278,29 @@ __global__ __launch_bounds__(1024) void k_dots(int64_t n, int64_t npk, int ncol,
 #pragma unroll
     for (int r = 0; r < V; ++r) xv[r] = (act && i0 + r < n) ? Conv<TX>::ld(x[i0 + r]) : 0.0;
     const TV* col0 = U + i0;
-    for (int l0 = 0; l0 < ncol; l0 += 8) {
-      double v[8];
+    auto walk = [&](auto keep, int l0, int l1) {  // columns l0 .. l1 - 1 (see kept_columns)
+      for (; l0 < l1; l0 += 8) {
+        double v[8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        v[q] = 0.0;
-        if (act && l0 + q < ncol) {
-          Pack16<TV> p;
-          p.raw = __builtin_nontemporal_load((const u32x4*)(col0 + (int64_t)(l0 + q) * ldu));
+        for (int q = 0; q < 8; ++q) {
+          v[q] = 0.0;
+          if (act && l0 + q < ncol) {
+            Pack16<TV> p;
+            const u32x4* src = (const u32x4*)(col0 + (int64_t)(l0 + q) * ldu);
+            if constexpr (decltype(keep)::value) p.raw = *src;
+            else p.raw = __builtin_nontemporal_load(src);
 #pragma unroll
-          for (int r = 0; r < V; ++r) v[q] += Conv<TV>::ld(p.v[r]) * xv[r];
+            for (int r = 0; r < V; ++r) v[q] += Conv<TV>::ld(p.v[r]) * xv[r];
+          }
         }
+        const double sv = wave_sum8(v, lane);
+        const int c = l0 + ((lane >> 3) & 7);
+        if ((lane & 7) == 0 && c < ncol) bins[wv][c] += sv;
       }
-      const double sv = wave_sum8(v, lane);
-      const int c = l0 + ((lane >> 3) & 7);
-      if ((lane & 7) == 0 && c < ncol) bins[wv][c] += sv;
-    }
+    };
+    const int lk = min(nkeep, ncol);
+    walk(std::true_type(), 0, lk);
+    walk(std::false_type(), lk, ncol);
   }
   __syncthreads();
   const int nw = blockDim.x >> 6;
@@ -1911,6 +1939,28 @@ void launch_ls(const LaunchEnv& e, int t, int pending, int finalize_only, const 
                                    scal, flags, bd_rel);
 }
 
+// Leading basis columns that a pass over ncol of them reads with plain loads,
+// so that they stay in the 256 MB Infinity Cache until the next step's pass (a
+// multiple of 8, the groups of the column walk); the others are read non-
+// temporally and leave the cache alone.  Reading every column non-temporally
+// puts the whole pass on HBM; reading more of them plainly than fit evicts
+// each before it is read again (least recently used over a cyclic walk), and
+// A, x and w want a share too.  All are kept up to 320 MB (a step's later
+// columns then still find most of the earlier ones), beyond that about 160 MB
+// of them.  Measured, microseconds per launch, all non-temporal / this rule /
+// 200 MB kept / all plain: 777^2 FP64 (m = 60) 45.2 / 38.8 / 38.8 / 38.8; 1000^2
+// FP64 59.2 / 54.5 / 54.2 / 62.7; 101^3 FP64 (m = 90) 90.8 / 82.3 / 83.9 /
+// 88; 101^3 pair 74.4 / 73.3 / 74.1 / 80; deterministic Krylov-Schur on 300,000 rows
+// (m = 80) update 23.9 / 20.3, dots 34.2 / 24.2; on 10^6 rows 67.6 / 62.5 and
+// 63.1 / 61.4.  The rolling window keeps none: its columns are 13 MB or more,
+// and keeping 8 of them gained nothing (128^3, 2 10^6 rows) or cost the SpMV
+// more than it gained (160^3: 326 to 322, SpMV 49 to 53).
+static int kept_columns(const LaunchEnv& e, int ncol) {
+  const double col = (double)e.n * (e.prec == 3 ? 6 : e.vbytes());
+  if (ncol * col <= 320e6) return (ncol + 7) & ~7;
+  return (int)(160e6 / col) & ~7;
+}
+
 int launch_update(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, const void* w, const double* coef,
                   void* unew, double* spart) {
   const int V = 16 / e.vbytes();
@@ -1918,18 +1968,19 @@ int launch_update(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, cons
   const int G = grid_for(npk, 1024, kMaxG);
   dim3 grid(G), block(1024);
   const size_t lds = bins_lds(e, 16, e.sp_kind != 0);
+  const int nkeep = kept_columns(e, ncol);
   if (e.prec == 0) {
     RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_update<double, double, KIND>, lds);
                       k_update<double, double, KIND><<<grid, block, lds, e.stream>>>(
-                          e.n, npk, ncol, (const double*)U, ldu, (const double*)w, coef, (double*)unew, spart, e.sp));
+                          e.n, npk, ncol, (const double*)U, ldu, (const double*)w, coef, (double*)unew, spart, e.sp, nkeep));
   } else if (e.prec == 1) {
     RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_update<float, float, KIND>, lds);
                       k_update<float, float, KIND><<<grid, block, lds, e.stream>>>(
-                          e.n, npk, ncol, (const float*)U, ldu, (const float*)w, coef, (float*)unew, spart, e.sp));
+                          e.n, npk, ncol, (const float*)U, ldu, (const float*)w, coef, (float*)unew, spart, e.sp, nkeep));
   } else {
     RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_update<bf16_t, float, KIND>, lds);
                       k_update<bf16_t, float, KIND><<<grid, block, lds, e.stream>>>(
-                          e.n, npk, ncol, (const bf16_t*)U, ldu, (const float*)w, coef, (bf16_t*)unew, spart, e.sp));
+                          e.n, npk, ncol, (const bf16_t*)U, ldu, (const float*)w, coef, (bf16_t*)unew, spart, e.sp, nkeep));
   }
   if (e.sp_kind == 0) {  // sketch of the stored value
     if (e.prec == 0) return gauss_t<double>(e, (const double*)unew, spart);
@@ -1943,14 +1994,14 @@ template <typename TV, typename TW, bool PRE, int PB, bool ROLL, bool SPLIT>
 static void ls_update_t(const LaunchEnv& e, dim3 grid, size_t lds, int t, int pending, const double* zraw,
                         const double* sraw, double* S, double* B, int ldb, double* E, double* cs, double* coef,
                         double* scal, int* flags, double bd_rel, int64_t npk, const void* U, int64_t ldu,
-                        const void* w, void* unew, double* spart) {
+                        const void* w, void* unew, double* spart, int nkeep) {
   const int16_t* Ulo = SPLIT ? e.lo_of(U) : nullptr;
   int16_t* unew_lo = SPLIT ? e.lo_of(unew) : nullptr;
   double* xout = SPLIT ? e.xcur : nullptr;
   RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_ls_update<TV, TW, KIND, PRE, PB, ROLL, SPLIT>, lds);
                     launch_k(e, true, !gauss_here(e), k_ls_update<TV, TW, KIND, PRE, PB, ROLL, SPLIT>, grid, dim3(1024),
                              lds, t, e.sp.d, pending, zraw, sraw, S, B, ldb, E, cs, coef, scal, flags, bd_rel, e.n,
-                             npk, (const TV*)U, ldu, (const TW*)w, (TV*)unew, spart, e.sp, Ulo, unew_lo, xout));
+                             npk, (const TV*)U, ldu, (const TW*)w, (TV*)unew, spart, e.sp, Ulo, unew_lo, xout, nkeep));
 }
 
 int launch_ls_update(const LaunchEnv& e, int t, int pending, const double* zraw, const double* sraw, double* S,
@@ -1979,13 +2030,14 @@ int launch_ls_update(const LaunchEnv& e, int t, int pending, const double* zraw,
   // (the pair basis takes no prefetch: its loads of two arrays leave no
   // registers for it)
   const bool roll = !pre && passes >= 4;
-#define RKS_LSU_PB(TV, TW, PB, SP)                                                                                    \
-  (pre && !SP ? ls_update_t<TV, TW, true, PB, false, SP>(e, dim3(G), lds, t, pending, zraw, sraw, S, B, ldb, E, cs,   \
-                                                         coef, scal, flags, bd_rel, npk, U, ldu, w, unew, spart)     \
-   : roll ? ls_update_t<TV, TW, false, PB, true, SP>(e, dim3(G), lds, t, pending, zraw, sraw, S, B, ldb, E, cs, coef, \
-                                                     scal, flags, bd_rel, npk, U, ldu, w, unew, spart)               \
-          : ls_update_t<TV, TW, false, PB, false, SP>(e, dim3(G), lds, t, pending, zraw, sraw, S, B, ldb, E, cs,      \
-                                                      coef, scal, flags, bd_rel, npk, U, ldu, w, unew, spart))
+  const int nkeep = kept_columns(e, t + 2);
+#define RKS_LSU_T(TV, TW, PRE, PB, ROLL, SP)                                                                    \
+  ls_update_t<TV, TW, PRE, PB, ROLL, SP>(e, dim3(G), lds, t, pending, zraw, sraw, S, B, ldb, E, cs, coef, scal, \
+                                         flags, bd_rel, npk, U, ldu, w, unew, spart, nkeep)
+#define RKS_LSU_PB(TV, TW, PB, SP)                            \
+  (pre && !SP ? RKS_LSU_T(TV, TW, true, PB, false, SP)        \
+   : roll     ? RKS_LSU_T(TV, TW, false, PB, true, SP)        \
+              : RKS_LSU_T(TV, TW, false, PB, false, SP))
 #define RKS_LSU(TV, TW, SP) (PBy == 8 ? RKS_LSU_PB(TV, TW, 8, SP) : RKS_LSU_PB(TV, TW, 16, SP))
   if (e.prec == 0) RKS_LSU(double, double, false);
   else if (e.prec == 1) RKS_LSU(float, float, false);
@@ -1993,6 +2045,7 @@ int launch_ls_update(const LaunchEnv& e, int t, int pending, const double* zraw,
   else RKS_LSU(float, double, true);
 #undef RKS_LSU
 #undef RKS_LSU_PB
+#undef RKS_LSU_T
   if (gauss_here(e)) {  // sketch of the stored value (the pair basis: of its FP64 copy)
     if (e.prec == 0) return gauss_t<double>(e, (const double*)unew, spart);
     if (e.prec == 1) return gauss_t<float>(e, (const float*)unew, spart);
@@ -2118,14 +2171,15 @@ int launch_dots(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, const 
   const int V = 16 / e.vbytes();
   const int64_t npk = (e.n + V - 1) / V;
   const int G = grid_for(npk, 1024, kMaxG);
+  const int nkeep = kept_columns(e, ncol);
   if (e.prec == 0) {
-    k_dots<double, double><<<G, 1024, 0, e.stream>>>(e.n, npk, ncol, (const double*)U, ldu, (const double*)x, part);
+    k_dots<double, double><<<G, 1024, 0, e.stream>>>(e.n, npk, ncol, (const double*)U, ldu, (const double*)x, part, nkeep);
   } else if (e.prec == 1) {
-    k_dots<float, float><<<G, 1024, 0, e.stream>>>(e.n, npk, ncol, (const float*)U, ldu, (const float*)x, part);
+    k_dots<float, float><<<G, 1024, 0, e.stream>>>(e.n, npk, ncol, (const float*)U, ldu, (const float*)x, part, nkeep);
   } else if (x_is_basis) {
-    k_dots<bf16_t, bf16_t><<<G, 1024, 0, e.stream>>>(e.n, npk, ncol, (const bf16_t*)U, ldu, (const bf16_t*)x, part);
+    k_dots<bf16_t, bf16_t><<<G, 1024, 0, e.stream>>>(e.n, npk, ncol, (const bf16_t*)U, ldu, (const bf16_t*)x, part, nkeep);
   } else {
-    k_dots<bf16_t, float><<<G, 1024, 0, e.stream>>>(e.n, npk, ncol, (const bf16_t*)U, ldu, (const float*)x, part);
+    k_dots<bf16_t, float><<<G, 1024, 0, e.stream>>>(e.n, npk, ncol, (const bf16_t*)U, ldu, (const float*)x, part, nkeep);
   }
   return G;
 }
