@@ -3,6 +3,7 @@
 #include "launch.hpp"
 
 #include <hip/hip_ext.h>
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 #include <unordered_map>
@@ -1595,40 +1596,233 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(YG || (SPLI
   }
 }
 
-// Residual pieces for one Ritz pair: with r = AX_a - re X_a + im X_b and, for
-// a complex pair, r2 = AX_b - re X_b - im X_a; per-block partial sums of
-// ||r||^2 + ||r2||^2 and ||X_a||^2 + ||X_b||^2.
-__global__ __launch_bounds__(256) void k_resid(int64_t n, const double* __restrict__ xa, const double* __restrict__ xb,
-                                               const double* __restrict__ axa, const double* __restrict__ axb,
-                                               double re, double im, double* __restrict__ part) {
-  __shared__ double red[16];
-  double rr = 0.0, xx = 0.0;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const double a = xa[i];
-    if (xb) {
-      const double b = xb[i];
-      const double r1 = axa[i] - re * a + im * b;
-      const double r2 = axb[i] - re * b - im * a;
-      rr += r1 * r1 + r2 * r2;
-      xx += a * a + b * b;
-    } else {
-      const double r1 = axa[i] - re * a;
-      rr += r1 * r1;
-      xx += a * a;
-    }
-  }
-  rr = block_sum(rr, red);
-  xx = block_sum(xx, red);
-  if (threadIdx.x == 0) {
-    part[2 * blockIdx.x] = rr;
-    part[2 * blockIdx.x + 1] = xx;
+// Residual pieces of up to kResidV Ritz columns at once (ResidGroup), so that
+// A is read once for all of them and their A X never goes to memory: per
+// block, for each column v, the sums over its rows of r^2 and x^2, where
+// r = A x - re x for a real pair and, for the two columns a, b of a complex
+// one, A a - re a + im b and A b - re b - im a.  Row blockIdx.x of part (2 ke
+// sums per row) gets them at 2 (first + v) and 2 (first + v) + 1.
+// (One pair after the other, an SpMV that stored A x, a pass that read x and A
+// x again, and a pass that scaled x took 49 + 22 + 22 us per column on the
+// 160^3 operator and 265 + 14 + 12 on the 2M-row power-law one; together with
+// the scaling of all columns in one launch it is 40 and 149.)
+__device__ __forceinline__ void resid_add(const ResidGroup& g, const double (&ax)[kResidV], const double (&x)[kResidV],
+                                          double (&rr)[kResidV], double (&xx)[kResidV]) {
+#pragma unroll
+  for (int v = 0; v < kResidV; ++v) {
+    double r = ax[v] - g.re[v] * x[v];
+    if (g.kind[v] == 1 && v + 1 < kResidV) r += g.im[v] * x[v + 1 < kResidV ? v + 1 : v];
+    if (g.kind[v] == 2 && v > 0) r -= g.im[v] * x[v > 0 ? v - 1 : v];
+    rr[v] += r * r;
+    xx[v] += x[v] * x[v];
   }
 }
 
-__global__ __launch_bounds__(256) void k_scale(int64_t n, double* __restrict__ x, double s) {
+// The block's sums to its row of part, waves added in order.
+__device__ __forceinline__ void resid_store(const ResidGroup& g, const double (&rr)[kResidV],
+                                            const double (&xx)[kResidV], double* __restrict__ part, int ke) {
+  __shared__ double red[4][2 * kResidV];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const double a = wave_sum8(rr, lane), b = wave_sum8(xx, lane);
+  if ((lane & 7) == 0) {
+    red[wv][2 * (lane >> 3)] = a;
+    red[wv][2 * (lane >> 3) + 1] = b;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < 2 * g.nc) {
+    const int q = threadIdx.x;
+    part[(size_t)blockIdx.x * 2 * ke + 2 * g.first + q] = ((red[0][q] + red[1][q]) + red[2][q]) + red[3][q];
+  }
+}
+
+// Sliced layout: a lane owns a row, as in k_spmv_sell, and gathers the columns
+// of X (leading dimension n) one after the other; on a banded matrix the
+// gathers of a wave are contiguous in each.
+template <typename TS>
+__global__ __launch_bounds__(256) void k_resid_sell(const int* __restrict__ rp, const int64_t* __restrict__ sl_off,
+                                                    int nsl, const int* __restrict__ col, const TS* __restrict__ val,
+                                                    const double* __restrict__ vtab, int64_t n,
+                                                    const double* __restrict__ X, ResidGroup g,
+                                                    double* __restrict__ part, int ke, int pad0) {
+  __shared__ double vt[sizeof(TS) == 1 ? 256 : 1];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if constexpr (sizeof(TS) == 1) {
+    vt[threadIdx.x] = vtab[threadIdx.x];
+    __syncthreads();
+  }
+  const double* x[kResidV];
+#pragma unroll
+  for (int v = 0; v < kResidV; ++v) x[v] = X + (int64_t)(g.first + (v < g.nc ? v : 0)) * n;
+  double rr[kResidV], xx[kResidV];
+#pragma unroll
+  for (int v = 0; v < kResidV; ++v) rr[v] = xx[v] = 0.0;
+  // contiguous eighths of the slices per XCD, as in k_spmv_sell
+  const int xcd = blockIdx.x & 7, lb = blockIdx.x >> 3, Gx = gridDim.x >> 3;
+  const int chunk = (nsl + 7) >> 3;
+  const int send = min(nsl, (xcd + 1) * chunk);
+  for (int s = xcd * chunk + lb * 4 + wv; s < send; s += Gx * 4) {
+    const int64_t b0 = sl_off[s];  // wave-uniform
+    const int slen = (int)((sl_off[s + 1] - b0) / kSliceRows);
+    const int64_t r = (int64_t)s * kSliceRows + lane;
+    const int len = pad0 ? slen : (r < n ? rp[r + 1] - rp[r] : 0);
+    double ax[kResidV], xr[kResidV];
+#pragma unroll
+    for (int v = 0; v < kResidV; ++v) {
+      ax[v] = 0.0;
+      xr[v] = v < g.nc && r < n ? x[v][r] : 0.0;
+    }
+    for (int k0 = 0; k0 < slen; k0 += 8) {
+      int cc[8];
+      double av[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int64_t e = b0 + (int64_t)kSliceRows * (k0 + q < slen ? k0 + q : slen - 1) + lane;
+        cc[q] = col[e];
+        if constexpr (sizeof(TS) == 1) av[q] = vt[val[e]];
+        else av[q] = val[e];
+      }
+#pragma unroll
+      for (int v = 0; v < kResidV; ++v)
+        if (v < g.nc) {
+          double xv[8];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) xv[q] = x[v][cc[q]];
+#pragma unroll
+          for (int q = 0; q < 8; ++q)
+            if (k0 + q < len) ax[v] += av[q] * xv[q];
+        }
+    }
+    resid_add(g, ax, xr, rr, xx);
+  }
+  resid_store(g, rr, xx, part, ke);
+}
+
+// Xi(row, v) = X(row, first + v) for v < nc, 0 for the others: kResidV
+// consecutive values (64 bytes) per row.
+__global__ __launch_bounds__(256) void k_interleave(int64_t n, const double* __restrict__ X, int first, int nc,
+                                                    double* __restrict__ Xi) {
+  typedef double d2v __attribute__((ext_vector_type(2)));
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) x[i] *= s;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    double v[kResidV];
+#pragma unroll
+    for (int q = 0; q < kResidV; ++q) v[q] = q < nc ? X[(int64_t)(first + q) * n + i] : 0.0;
+#pragma unroll
+    for (int q = 0; q < kResidV / 2; ++q) *(d2v*)(Xi + i * kResidV + 2 * q) = (d2v){v[2 * q], v[2 * q + 1]};
+  }
+}
+
+// Any CSR matrix: 8 slots per wave, each with one lane per column of the
+// interleaved Xi, so that a gather is one 64-byte piece for all the columns
+// instead of a line for each.  A slot owns the rows that start in its equal
+// share of the nonzeros and walks their nonzeros as one sequence, kResidU
+// loads and gathers at a time, whatever the rows' lengths (one row per slot
+// with a common trip count waits for the longest of 8: 1.54 ms for 8 columns
+// of the 2M-row power-law operator against 0.92, 4.8 TB/s of 128-byte lines).  A row's products are added in
+// order.  The other column of a complex pair is the neighbouring lane's.
+constexpr int kResidU = 8;
+
+__global__ __launch_bounds__(256) void k_resid_csr(const int* __restrict__ rp, const int* __restrict__ col,
+                                                   const double* __restrict__ val, int64_t n, int64_t nnz,
+                                                   const double* __restrict__ Xi, ResidGroup g,
+                                                   double* __restrict__ part, int ke) {
+  const int lane = threadIdx.x & 63, v = lane & 7;
+  const int64_t slot = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 3;
+  const int64_t nslot = ((int64_t)gridDim.x * blockDim.x) >> 3;
+  double re = 0.0, im = 0.0;
+  int kind = 0;
+#pragma unroll
+  for (int q = 0; q < kResidV; ++q)
+    if (q == v) {
+      re = g.re[q];
+      kind = g.kind[q];
+      im = kind == 1 ? g.im[q] : (kind == 2 ? -g.im[q] : 0.0);
+    }
+  // the first row that starts at or after nonzero e
+  auto row_at = [&](int64_t e) {
+    int64_t lo = 0, hi = n;
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) >> 1;
+      if (rp[mid] < e) lo = mid + 1;
+      else hi = mid;
+    }
+    return lo;
+  };
+  const int64_t share = (nnz + nslot - 1) / nslot;
+  int64_t r = row_at(min(nnz, slot * share));
+  const int64_t r1 = slot + 1 == nslot ? n : row_at(min(nnz, (slot + 1) * share));
+  double rr = 0.0, xx = 0.0;
+  if (r < r1) {
+    int e = rp[r], rend = rp[r + 1], rnext = rp[r + 2 <= n ? r + 2 : n];
+    const int et = rp[r1];
+    double x = Xi[r * kResidV + v], xn = Xi[(r + 1 < n ? r + 1 : r) * kResidV + v], ax = 0.0;
+    // rows that end at nonzero e1: the current one, and empty ones behind it
+    auto finish = [&](int e1) {
+      while (r < r1 && rend == e1) {
+        const double p1 = __shfl_down(x, 1), p2 = __shfl_up(x, 1);
+        double res = ax - re * x;
+        if (kind == 1) res += im * p1;
+        if (kind == 2) res += im * p2;
+        rr += res * res;
+        xx += x * x;
+        ax = 0.0;
+        ++r;
+        rend = rnext;
+        x = xn;
+        rnext = rp[r + 2 <= n ? r + 2 : n];
+        xn = Xi[(r + 1 < n ? r + 1 : n - 1) * kResidV + v];
+      }
+    };
+    finish(e);  // leading empty rows
+    for (; e < et; e += kResidU) {
+      double a[kResidU], xv[kResidU];
+      int c[kResidU];
+#pragma unroll
+      for (int q = 0; q < kResidU; ++q) {
+        const int eq = e + q < et ? e + q : e;
+        c[q] = col[eq];
+        a[q] = val[eq];
+      }
+#pragma unroll
+      for (int q = 0; q < kResidU; ++q) xv[q] = Xi[(int64_t)c[q] * kResidV + v];
+#pragma unroll
+      for (int q = 0; q < kResidU; ++q)
+        if (e + q < et) {
+          ax += a[q] * xv[q];
+          finish(e + q + 1);
+        }
+    }
+  }
+  // the 8 slots of a wave, then its 4 waves, in order
+#pragma unroll
+  for (int d = 8; d < 64; d <<= 1) {
+    rr += __shfl_xor(rr, d);
+    xx += __shfl_xor(xx, d);
+  }
+  __shared__ double red[4][2 * kResidV];
+  if (lane < kResidV) {
+    red[threadIdx.x >> 6][2 * lane] = rr;
+    red[threadIdx.x >> 6][2 * lane + 1] = xx;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < 2 * g.nc) {
+    const int q = threadIdx.x;
+    part[(size_t)blockIdx.x * 2 * ke + 2 * g.first + q] = ((red[0][q] + red[1][q]) + red[2][q]) + red[3][q];
+  }
+}
+
+// X(:, c) *= 1 / sqrt(sum of squares of its pair), sums as reduced from part.
+__global__ __launch_bounds__(256) void k_normalise(int64_t n, double* __restrict__ X, const double* __restrict__ sums,
+                                                   PairKinds kinds) {
+  const int c = blockIdx.y, kd = kinds.kind[c];
+  double xx = sums[2 * c + 1];
+  if (kd == 1) xx += sums[2 * c + 3];
+  if (kd == 2) xx = sums[2 * c - 1] + xx;
+  const double sc = 1.0 / sqrt(xx);
+  double* x = X + (int64_t)c * n;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) x[i] *= sc;
 }
 
 __global__ __launch_bounds__(256) void k_fill(int64_t n, double* __restrict__ x, double v) {
@@ -2175,15 +2369,38 @@ void launch_rotate(const LaunchEnv& e, const void* U, int64_t ldu, int in0, int 
   }
 }
 
-int launch_resid(const LaunchEnv& e, const double* xa, const double* xb, const double* axa, const double* axb,
-                 double re, double im, double* part) {
-  const int G = grid_for(e.n, 256, kMaxG);
-  k_resid<<<G, 256, 0, e.stream>>>(e.n, xa, xb, axa, axb, re, im, part);
+int launch_resid(const LaunchEnv& e, int64_t nnz, const double* X, int ke, const int* kind, const double* re,
+                 const double* im, double* Xi, double* part) {
+  // (a multiple of 8: the slices are dealt to the XCDs)
+  const int G = (grid_for(e.sl ? e.nsl : (std::max(nnz, 64 * e.n / 8) + 511) / 512, 4, kResidMaxG) + 7) & ~7;
+  for (int c = 0; c < ke;) {
+    ResidGroup g{};
+    g.first = c;
+    while (c < ke && g.nc < kResidV && !(kind[c] == 1 && g.nc + 1 == kResidV)) {  // a complex pair stays together
+      g.kind[g.nc] = kind[c];
+      g.re[g.nc] = re[c];
+      g.im[g.nc] = kind[c] == 2 ? im[c - 1] : im[c];
+      ++g.nc;
+      ++c;
+    }
+    if (e.sl && e.vidx_sl) {
+      k_resid_sell<uint8_t><<<G, 256, 0, e.stream>>>(e.rp, e.sl_off, e.nsl, e.col_sl, e.vidx_sl, e.vtab, e.n, X, g,
+                                                     part, ke, e.sl_pad0);
+    } else if (e.sl) {
+      k_resid_sell<double><<<G, 256, 0, e.stream>>>(e.rp, e.sl_off, e.nsl, e.col_sl, e.val_sl, nullptr, e.n, X, g,
+                                                    part, ke, e.sl_pad0);
+    } else {
+      k_interleave<<<grid_for(e.n, 256, 4096), 256, 0, e.stream>>>(e.n, X, g.first, g.nc, Xi);
+      k_resid_csr<<<G, 256, 0, e.stream>>>(e.rp, e.col, e.val, e.n, nnz, Xi, g, part, ke);
+    }
+  }
   return G;
 }
 
-void launch_scale(const LaunchEnv& e, double* x, double s) {
-  k_scale<<<grid_for(e.n, 256, kMaxG), 256, 0, e.stream>>>(e.n, x, s);
+void launch_normalise(const LaunchEnv& e, double* X, int ke, const int* kind, const double* sums) {
+  PairKinds k{};
+  for (int c = 0; c < ke; ++c) k.kind[c] = (int8_t)kind[c];
+  k_normalise<<<dim3(grid_for(e.n, 1024, 256), ke), 256, 0, e.stream>>>(e.n, X, sums, k);
 }
 
 int launch_dots(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, const void* x, int x_is_basis, double* part) {

@@ -59,6 +59,20 @@ struct Conv<bf16_t> {
   }
 };
 
+// Up to kResidV consecutive Ritz columns whose residuals are formed together:
+// columns first .. first + nc - 1 of X, of kind 0 (real), 1 and 2 (real and
+// imaginary part of a complex pair, both in the group), their eigenvalues.
+constexpr int kResidV = 8;
+constexpr int kResidMaxG = 2048;  // workgroups, and partial rows, at most
+struct ResidGroup {
+  int first, nc;
+  int kind[kResidV];
+  double re[kResidV], im[kResidV];
+};
+struct PairKinds {
+  int8_t kind[kRotMax];
+};
+
 struct SketchP {
   int d;
   int zeta;

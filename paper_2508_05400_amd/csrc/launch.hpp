@@ -108,9 +108,16 @@ int launch_init(const LaunchEnv& e, void* u, const double* u0, uint32_t s0, uint
 // 128 (the kernel reads whole row tiles up to ldu); O's rows >= n are not written.
 void launch_rotate(const LaunchEnv& e, const void* U, int64_t ldu, int in0, int min, void* O, int64_t ldo, int out0,
                    int kout, const double* Y, int xsrc, int xdst, double xscale, int out_fp64);
-int launch_resid(const LaunchEnv& e, const double* xa, const double* xb, const double* axa, const double* axb,
-                 double re, double im, double* part);
-void launch_scale(const LaunchEnv& e, double* x, double s);
+// Squared norms of the FP64 residuals of the ke <= kRotMax Ritz columns of X
+// (leading dimension n) and of the columns themselves, as partial rows of part
+// (2 ke per row: of column c at 2 c and 2 c + 1); returns the number of rows
+// (at most kResidMaxG).  kind: 0 a real pair, 1 and 2 the real and the imaginary
+// part of a complex one, whose eigenvalue is read at the first.  Xi: scratch
+// of n kResidV values, unused in the sliced layout.
+int launch_resid(const LaunchEnv& e, int64_t nnz, const double* X, int ke, const int* kind, const double* re,
+                 const double* im, double* Xi, double* part);
+// Scales every pair of X to unit norm, sums being the sums of launch_resid's rows.
+void launch_normalise(const LaunchEnv& e, double* X, int ke, const int* kind, const double* sums);
 void launch_fill(const LaunchEnv& e, int64_t len, double* x, double v);
 void launch_copy16(hipStream_t stream, const void* src, void* dst, int64_t packets);
 void launch_read16(hipStream_t stream, const void* src, int64_t packets);

@@ -95,7 +95,7 @@ struct rks_ctx {
   uint16_t* off_pn = nullptr;
   double* val_pn = nullptr;
   float* val32_pn = nullptr;
-  double *Xr = nullptr, *ax1 = nullptr, *ax2 = nullptr, *rpart = nullptr;  // residual scratch (lazy)
+  double *Xr = nullptr, *Xi = nullptr, *rpart = nullptr;  // residual scratch (lazy)
   // E, B, S, cs and flags live in one device block and one pinned host block
   // of the same layout, so a restart moves them with one copy each way
   void* dstate = nullptr;
@@ -836,9 +836,10 @@ Packed pack_ritz(const rks_ctx* c) {
 int ensure_resid_scratch(rks_ctx* c) {
   const size_t cols = (size_t)c->k + 1;
   if (!c->Xr && hipMalloc(&c->Xr, (size_t)c->n * cols * 8) != hipSuccess) return fail(c, RKS_ENOMEM, "residual X");
-  if (!c->ax1 && hipMalloc(&c->ax1, (size_t)c->n * 8) != hipSuccess) return fail(c, RKS_ENOMEM, "residual AX");
-  if (!c->ax2 && hipMalloc(&c->ax2, (size_t)c->n * 8) != hipSuccess) return fail(c, RKS_ENOMEM, "residual AX");
-  if (!c->rpart && hipMalloc(&c->rpart, cols * 2 * rks::kMaxG * 8) != hipSuccess)
+  if (!c->Xi && !c->env.sl && hipMalloc(&c->Xi, (size_t)c->n * rks::kResidV * 8) != hipSuccess)
+    return fail(c, RKS_ENOMEM, "residual X, interleaved");
+  // partial rows, then their sums
+  if (!c->rpart && hipMalloc(&c->rpart, cols * 2 * (rks::kResidMaxG + 1) * 8) != hipSuccess)
     return fail(c, RKS_ENOMEM, "residual partials");
   return RKS_OK;
 }
@@ -850,53 +851,36 @@ int device_residuals(rks_ctx* c, const Packed& P, double* Xd, double* resid, boo
   const int ke = c->kr;
   const int64_t n = c->n;
   HIPCHK(c, hipStreamSynchronize(stm));  // the pinned staging buffer hY may still be in flight
-  for (int c0 = 0; c0 < ke; c0 += rks::kRotMax) {
-    const int kc = std::min(rks::kRotMax, ke - c0);
-    for (int jj = 0; jj < kc; ++jj)
-      for (int r = 0; r < ke; ++r) c->hY[r + (size_t)jj * ke] = P.W[r + (size_t)(c0 + jj) * ke];
-    HIPCHK(c, hipMemcpyAsync(c->Yd, c->hY, (size_t)ke * kc * 8, hipMemcpyHostToDevice, stm));
-    rks::launch_rotate(c->env, c->U, c->ldu, 0, ke, Xd, n, c0, kc, c->Yd, -1, 0, 0.0, 1);
-    HIPCHK(c, hipStreamSynchronize(stm));  // hY is reused by the next chunk
+  std::memcpy(c->hY, P.W.data(), (size_t)ke * ke * 8);
+  HIPCHK(c, hipMemcpyAsync(c->Yd, c->hY, (size_t)ke * ke * 8, hipMemcpyHostToDevice, stm));
+  rks::launch_rotate(c->env, c->U, c->ldu, 0, ke, Xd, n, 0, ke, c->Yd, -1, 0, 0.0, 1);
+  std::vector<double> re(ke), im(ke);
+  for (int i = 0; i < ke; ++i) {
+    re[i] = P.lam[i].real();
+    im[i] = P.lam[i].imag();
+    if (P.pair_of[i] == 2) re[i] = re[i - 1];
   }
-  // every pair's products and partial sums first (slot s of rpart, stride
-  // 2 G), then one copy and one synchronisation for all of them; the AX
-  // buffers are reused in stream order
-  std::vector<int> first;
-  int G = 0;
-  for (int i = 0; i < ke;) {
-    const bool cp = P.pair_of[i] == 1;
-    double* xa = Xd + (size_t)i * n;
-    double* xb = cp ? Xd + (size_t)(i + 1) * n : nullptr;
-    rks::launch_spmv_sketch(c->env, xa, c->ax1, nullptr, 0, 0);
-    if (cp) rks::launch_spmv_sketch(c->env, xb, c->ax2, nullptr, 0, 0);
-    G = rks::launch_resid(c->env, xa, xb, c->ax1, cp ? c->ax2 : nullptr, P.lam[i].real(), P.lam[i].imag(),
-                          c->rpart + first.size() * 2 * rks::kMaxG);
-    first.push_back(i);
-    i += cp ? 2 : 1;
-  }
+  double* sums = c->rpart + (size_t)rks::kResidMaxG * 2 * ke;
+  const int G = rks::launch_resid(c->env, c->nnz, Xd, ke, P.pair_of.data(), re.data(), im.data(), c->Xi, c->rpart);
+  rks::launch_reduce_len(c->env, c->rpart, G, sums, 2 * ke);
+  if (normalise) rks::launch_normalise(c->env, Xd, ke, P.pair_of.data(), sums);
   HIPCHK(c, hipGetLastError());
-  std::vector<double> hpart(first.size() * 2 * rks::kMaxG);
-  HIPCHK(c, hipMemcpyAsync(hpart.data(), c->rpart, hpart.size() * 8, hipMemcpyDeviceToHost, stm));
+  // (hY: its upload above comes before this copy in the stream)
+  HIPCHK(c, hipMemcpyAsync(c->hY, sums, (size_t)2 * ke * 8, hipMemcpyDeviceToHost, stm));
   HIPCHK(c, hipStreamSynchronize(stm));
-  for (size_t sl = 0; sl < first.size(); ++sl) {
-    const int i = first[sl];
+  for (int i = 0; i < ke; ++i) {
+    double rr = c->hY[2 * i], xx = c->hY[2 * i + 1];
     const bool cp = P.pair_of[i] == 1;
-    const double* hp = &hpart[sl * 2 * rks::kMaxG];
-    double rr = 0.0, xx = 0.0;
-    for (int g = 0; g < G; ++g) {
-      rr += hp[2 * g];
-      xx += hp[2 * g + 1];
+    if (cp) {
+      rr += c->hY[2 * i + 2];
+      xx += c->hY[2 * i + 3];
     }
-    const double res = std::sqrt(rr) / (c->normA1 * std::sqrt(xx));
-    if (normalise) {
-      const double sc = 1.0 / std::sqrt(xx);
-      rks::launch_scale(c->env, Xd + (size_t)i * n, sc);
-      if (cp) rks::launch_scale(c->env, Xd + (size_t)(i + 1) * n, sc);
+    resid[i] = std::sqrt(rr) / (c->normA1 * std::sqrt(xx));
+    if (cp) {
+      resid[i + 1] = resid[i];
+      ++i;
     }
-    resid[i] = res;
-    if (cp) resid[i + 1] = res;
   }
-  HIPCHK(c, hipGetLastError());
   return RKS_OK;
 }
 
@@ -1066,7 +1050,7 @@ void free_all(rks_ctx* c) {
   void* dev[] = {c->rp, c->col, c->tiles, c->dstate, c->val, c->val32, c->U_lo, c->U64, c->w, c->xcur,
                  c->coef, c->z, c->sr, c->zpart, c->spart, c->scal, c->Yd, c->u0tmp, c->kpart, c->om,
                  c->col_pn, c->tiles_pn, c->toff_pn, c->ptile, c->off_pn, c->val_pn, c->val32_pn,
-                 c->Xr, c->ax1, c->ax2, c->rpart, c->vidx, c->vtab, c->sl_off, c->col_sl, c->val_sl,
+                 c->Xr, c->Xi, c->rpart, c->vidx, c->vtab, c->sl_off, c->col_sl, c->val_sl,
                  c->vidx_sl, c->val32_sl};
   for (void* p : dev)
     if (p) (void)hipFree(p);
