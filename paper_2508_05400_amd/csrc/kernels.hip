@@ -65,6 +65,11 @@ __device__ __forceinline__ void bins_zero(double* bins, int d) {
   for (int b = threadIdx.x; b < nb; b += blockDim.x) bins[b] = 0.0;
 }
 
+// A wave's own d bins: needs no barrier before the wave adds to them.
+__device__ __forceinline__ void wave_bins_zero(double* wb, int d) {
+  for (int b = threadIdx.x & 63; b < d; b += 64) wb[b] = 0.0;
+}
+
 __device__ __forceinline__ void bins_store(const double* bins, double* part, int d, double scale) {
   const int nw = blockDim.x >> 6;
   for (int b = threadIdx.x; b < d; b += blockDim.x) {
@@ -233,10 +238,9 @@ __global__ __launch_bounds__(64 * kSpmvWaves) void k_spmv_sketch(const int* __re
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   bool tab = sizeof(TS) != 1;
-  if (do_sketch) bins_zero(bins, sp.d);
-  __syncthreads();
   TA* pw = prod[wv];
   double* wb = wave_bins(bins, sp.d);
+  if (do_sketch) wave_bins_zero(wb, sp.d);
   const int Gx = gridDim.x >> 3;
   int t0, tend, tstep;
   if (Gx > 0 && (gridDim.x & 7) == 0) {
@@ -325,8 +329,6 @@ __global__ __launch_bounds__(64 * kSpmvWaves) void k_spmv_sell(const int* __rest
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   bool tab = sizeof(TS) != 1;
-  if (do_sketch) bins_zero(bins, sp.d);
-  __syncthreads();
   double* wb = wave_bins(bins, sp.d);
   const int Gx = gridDim.x >> 3;
   int s0, send, sstep;
@@ -341,9 +343,21 @@ __global__ __launch_bounds__(64 * kSpmvWaves) void k_spmv_sell(const int* __rest
     send = nsl;
     sstep = gridDim.x * kSpmvWaves;
   }
+  // (wave-uniform) offsets of the slice, loaded one slice ahead
+  int64_t nb0 = 0, nb1 = 0;
+  if (s0 < send) {
+    nb0 = sl_off[s0];
+    nb1 = sl_off[s0 + 1];
+  }
+  if (do_sketch) wave_bins_zero(wb, sp.d);
   for (int s = s0; s < send; s += sstep) {
-    const int64_t b0 = sl_off[s];  // wave-uniform
-    const int slen = (int)((sl_off[s + 1] - b0) / kSliceRows);
+    const int64_t b0 = nb0;
+    const int slen = (int)((nb1 - b0) / kSliceRows);
+    {
+      const int sn = s + sstep < send ? s + sstep : s;
+      nb0 = sl_off[sn];
+      nb1 = sl_off[sn + 1];
+    }
     const int64_t r = (int64_t)s * kSliceRows + lane;
     const int len = pad0 ? slen : (r < n ? rp[r + 1] - rp[r] : 0);
     TA acc = 0;
@@ -530,8 +544,9 @@ __global__ __launch_bounds__(64 * kSpmvWaves) void k_spmv_panel(
 // chains; a fixed tree over the slices finishes the sum (same order every
 // call).  A wave reads 8 rows x 64 contiguous bytes per load.  128 slices
 // (10 rows each for the SpMV's 1,280 partial rows) took the launch from 4.8
-// to 4.0 us against 64 slices; 4 bins per block or 4 chains per slice did
-// not help further.
+// to 4.0 us against 64 slices; 4 bins per block, 4 chains per slice or 12
+// loads issued together did not help further.  The tree takes one barrier
+// (seven before: 4.2 to 3.9 us with 512 rows, 3.25 to 2.9 with 313).
 constexpr int kRedBins = 8;
 constexpr int kRedSl = 128;
 
@@ -556,11 +571,23 @@ __global__ __launch_bounds__(kRedBins * kRedSl) void k_reduce(const double* __re
   }
   red[sl][lb] = a0 + a1;
   __syncthreads();
-  for (int s = kRedSl / 2; s > 0; s >>= 1) {
-    if (sl < s) red[sl][lb] += red[sl + s][lb];
-    __syncthreads();
+  // the tree over the slices, 64, 32, .. 1 apart: a thread of the first wave
+  // adds the 16 slices sl, sl + 8, ... (sl < 8) down to 8 apart in registers,
+  // and the last three steps cross lanes
+  if (threadIdx.x < 64) {
+    double v[kRedSl / 8];
+#pragma unroll
+    for (int q = 0; q < kRedSl / 8; ++q) v[q] = red[sl + 8 * q][lb];
+#pragma unroll
+    for (int s = kRedSl / 16; s > 0; s >>= 1)
+#pragma unroll
+      for (int q = 0; q < s; ++q) v[q] += v[q + s];
+    double t = v[0];
+    t += __shfl_down(t, 4 * kRedBins);
+    t += __shfl_down(t, 2 * kRedBins);
+    t += __shfl_down(t, kRedBins);
+    if (sl == 0 && b < d) o[b] = t;
   }
-  if (sl == 0 && b < d) o[b] = red[0][lb];
 }
 
 // Finalise column t when pending (beta = ||s~||, S(:,t) = s~/beta, scale
@@ -1368,25 +1395,22 @@ __global__ void k_ks_finalize(int t, const double* __restrict__ h, const double*
 // breakdown), stored in TV when `store`; partials of Omega of the stored value.
 // SPLIT (TV = float): stored as the pair (u, ulo; see split_pair), the stored
 // value also to xout in FP64.
-template <typename TV, int KIND, bool SPLIT = false>
+// GEN: the vector is generated; otherwise it is u0, whose values are loaded
+// kInitU at a time.
+constexpr int kInitU = 4;
+
+template <typename TV, int KIND, bool SPLIT, bool GEN>
 __global__ __launch_bounds__(512) void k_init(int64_t n, TV* __restrict__ u, const double* __restrict__ u0,
                                               uint32_t s0, uint32_t s1, uint32_t c2, uint32_t tag,
                                               double* __restrict__ spart, SketchP sp, int store,
-                                              int16_t* __restrict__ ulo = nullptr, double* __restrict__ xout = nullptr) {
+                                              int16_t* __restrict__ ulo, double* __restrict__ xout) {
   extern __shared__ double bins[];  // 8 waves x d (none for KIND 3)
   if (KIND != 3) bins_zero(bins, sp.d);
   __syncthreads();
   double* wb = wave_bins(bins, sp.d);
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   double nrm = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    double v;
-    if (u0) {
-      v = u0[i];
-    } else {
-      double g1;
-      gauss_pair((uint64_t)i, c2, tag, s0, s1, v, g1);
-    }
+  auto row = [&](int64_t i, double v) {
     double vs;
     if constexpr (SPLIT) {
       float hi;
@@ -1405,6 +1429,23 @@ __global__ __launch_bounds__(512) void k_init(int64_t n, TV* __restrict__ u, con
     }
     if (KIND == 2) nrm += vs * vs;
     else sketch_add<KIND>(wb, (uint64_t)i, vs, sp);
+  };
+  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if constexpr (GEN) {
+    for (; i < n; i += stride) {
+      double v, g1;
+      gauss_pair((uint64_t)i, c2, tag, s0, s1, v, g1);
+      row(i, v);
+    }
+  } else {
+    for (; i < n; i += kInitU * stride) {
+      double v[kInitU];
+#pragma unroll
+      for (int q = 0; q < kInitU; ++q) v[q] = u0[i + q * stride < n ? i + q * stride : i];
+#pragma unroll
+      for (int q = 0; q < kInitU; ++q)
+        if (i + q * stride < n) row(i + q * stride, v[q]);
+    }
   }
   if (KIND == 2) {
     nrm = wave_sum(nrm);
@@ -2268,30 +2309,33 @@ int launch_ls_update(const LaunchEnv& e, int t, int pending, const double* zraw,
   return G;
 }
 
+template <typename TV, bool SPLIT>
+static void init_t(const LaunchEnv& e, int G, TV* u, const double* u0, uint32_t s0, uint32_t s1, uint32_t c2,
+                   uint32_t tag, double* spart, int store, int16_t* ulo, double* xout) {
+  const size_t lds = bins_lds(e, 8, e.sp_kind != 0);
+  if (u0) {
+    RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_init<TV, KIND, SPLIT, false>, lds);
+                      k_init<TV, KIND, SPLIT, false><<<G, 512, lds, e.stream>>>(e.n, u, u0, s0, s1, c2, tag, spart,
+                                                                             e.sp, store, ulo, xout));
+  } else {
+    RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_init<TV, KIND, SPLIT, true>, lds);
+                      k_init<TV, KIND, SPLIT, true><<<G, 512, lds, e.stream>>>(e.n, u, u0, s0, s1, c2, tag, spart, e.sp,
+                                                                            store, ulo, xout));
+  }
+}
+
 int launch_init(const LaunchEnv& e, void* u, const double* u0, uint32_t s0, uint32_t s1, double* spart, int store,
                 int prec_override, uint32_t c2, uint32_t tag) {
   const int prec = prec_override >= 0 ? prec_override : e.prec;
   const int G = grid_for(e.n, 512, kMaxG);
-  dim3 grid(G), block(512);
-  const size_t lds = bins_lds(e, 8, e.sp_kind != 0);
-  if (prec == 0) {
-    RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_init<double, KIND>, lds);
-                      k_init<double, KIND><<<grid, block, lds, e.stream>>>(e.n, (double*)u, u0, s0, s1, c2, tag, spart, e.sp,
-                                                                        store));
-  } else if (prec == 1) {
-    RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_init<float, KIND>, lds);
-                      k_init<float, KIND><<<grid, block, lds, e.stream>>>(e.n, (float*)u, u0, s0, s1, c2, tag, spart, e.sp,
-                                                                        store));
-  } else if (prec == 2) {
-    RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_init<bf16_t, KIND>, lds);
-                      k_init<bf16_t, KIND><<<grid, block, lds, e.stream>>>(e.n, (bf16_t*)u, u0, s0, s1, c2, tag, spart, e.sp,
-                                                                        store));
-  } else {
-    RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_init<float, KIND, true>, lds);
-                      k_init<float, KIND, true><<<grid, block, lds, e.stream>>>(
-                          e.n, (float*)u, u0, s0, s1, c2, tag, spart, e.sp, store, store ? e.lo_of(u) : nullptr,
-                          e.xcur));
-  }
+  if (prec == 0)
+    init_t<double, false>(e, G, (double*)u, u0, s0, s1, c2, tag, spart, store, nullptr, nullptr);
+  else if (prec == 1)
+    init_t<float, false>(e, G, (float*)u, u0, s0, s1, c2, tag, spart, store, nullptr, nullptr);
+  else if (prec == 2)
+    init_t<bf16_t, false>(e, G, (bf16_t*)u, u0, s0, s1, c2, tag, spart, store, nullptr, nullptr);
+  else
+    init_t<float, true>(e, G, (float*)u, u0, s0, s1, c2, tag, spart, store, store ? e.lo_of(u) : nullptr, e.xcur);
   if (e.sp_kind == 0 && !(store && e.gauss_apart)) {
     // sketch of the stored value; without a store, of u0 itself (FP64 only)
     if (!store) return u0 ? gauss_t<double>(e, u0, spart) : 0;
@@ -2475,7 +2519,8 @@ int launch_sketch_scratch(const LaunchEnv& e, const double* x, double* part, dou
   } else {
     G = grid_for(e.n, 512, kMaxG);
     const size_t lds = bins_lds(e, 8, true);
-    k_init<double, 1><<<G, 512, lds, e.stream>>>(e.n, nullptr, x, 0u, 0u, 0u, 2u, part, e.sp, 0);
+    k_init<double, 1, false, false><<<G, 512, lds, e.stream>>>(e.n, nullptr, x, 0u, 0u, 0u, 2u, part, e.sp, 0, nullptr,
+                                                               nullptr);
   }
   launch_reduce(e, part, G, nullptr, 0, z, nullptr);
   return G;
