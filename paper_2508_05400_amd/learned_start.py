@@ -33,6 +33,7 @@ import numpy as np
 from . import _binding as B
 
 LAYERS = [(2, 16, 1), (16, 16, 2), (16, 16, 4), (16, 16, 8), (16, 16, 16), (16, 1, 1)]  # (Cin, Cout, dilation)
+PARAMS = sum((9 * c + 1) * o for c, o, _ in LAYERS)
 GRID = 64
 KPAD = 17  # wanted pairs k = 16, or 17 when a conjugate pair straddles the boundary
 FAMILY = dict(N=512, k=16, m=48, d=192, which="SR", tol=1e-10, sketch="sparse", sketch_seed=5, start_seed=1)
@@ -60,6 +61,16 @@ def target_basis(X: np.ndarray, N: int) -> np.ndarray:
     return V
 
 
+def _one_range(tensors, like) -> bool:
+    """Whether the tensors follow one another in memory, with the sizes of those of like."""
+    at = tensors[0].data_ptr()
+    for t, p in zip(tensors, like):
+        if t.data_ptr() != at or t.numel() != p.numel() or t.element_size() != 4 or not t.is_contiguous():
+            return False
+        at += 4 * t.numel()
+    return len(tensors) == len(like)
+
+
 class StartNet:
     """Parameters and Adam state on the device; passes through rks_net_* kernels."""
 
@@ -67,23 +78,30 @@ class StartNet:
         import torch
         self.torch = torch
         rng = np.random.default_rng(seed)
-        self.w, self.b = [], []
-        for cin, cout, _ in LAYERS:
+        self.w, self.b = self._views(torch.zeros(PARAMS, dtype=torch.float32, device="cuda"))
+        for w, (cin, cout, _) in zip(self.w, LAYERS):
             std = np.sqrt(2.0 / (cin * 9))
-            self.w.append(torch.tensor(rng.standard_normal((cout, cin, 3, 3)) * std, dtype=torch.float32,
-                                       device="cuda"))
-            self.b.append(torch.zeros(cout, dtype=torch.float32, device="cuda"))
-        self.m = [torch.zeros_like(p) for p in self.w + self.b]
-        self.v = [torch.zeros_like(p) for p in self.w + self.b]
+            w.copy_(torch.tensor(rng.standard_normal((cout, cin, 3, 3)) * std, dtype=torch.float32))
+        self.m = sum(self._views(torch.zeros(PARAMS, dtype=torch.float32, device="cuda")), [])
+        self.v = sum(self._views(torch.zeros(PARAMS, dtype=torch.float32, device="cuda")), [])
         self.t = 0
+
+    @staticmethod
+    def _views(flat):
+        """Weights and biases of all layers as views of one buffer, in that order
+        (so that one Adam launch covers them; twelve took 54 of a 670 us step)."""
+        parts = flat.split([o * c * 9 for c, o, _ in LAYERS] + [o for _, o, _ in LAYERS])
+        return [p.view(o, c, 3, 3) for p, (c, o, _) in zip(parts, LAYERS)], list(parts[len(LAYERS):])
 
     def forward(self, x):
         """x: (Bn, 2, 64, 64) float32 device tensor -> list of activations."""
         torch = self.torch
-        acts = [x.contiguous()]
         Bn = x.shape[0]
-        for li, (cin, cout, dil) in enumerate(LAYERS):
-            y = torch.empty((Bn, cout, GRID, GRID), dtype=torch.float32, device="cuda")
+        # the hidden layers are alike: one allocation for their activations
+        outs = torch.empty((len(LAYERS) - 1, Bn, LAYERS[0][1], GRID, GRID), dtype=torch.float32, device="cuda").unbind(0)
+        outs += (torch.empty((Bn, LAYERS[-1][1], GRID, GRID), dtype=torch.float32, device="cuda"),)
+        acts = [x.contiguous()]
+        for li, ((cin, cout, dil), y) in enumerate(zip(LAYERS, outs)):
             B.rks_net_conv3x3_forward(acts[-1], self.w[li], self.b[li], y, Bn, cin, cout, GRID, GRID, dil,
                                       li + 1 < len(LAYERS))
             acts.append(y)
@@ -92,17 +110,14 @@ class StartNet:
     def backward(self, acts, dout):
         torch = self.torch
         Bn = acts[0].shape[0]
-        gw, gb = [None] * len(LAYERS), [None] * len(LAYERS)
+        gw, gb = self._views(torch.empty(PARAMS, dtype=torch.float32, device="cuda"))
         g = dout.contiguous()
         for li in reversed(range(len(LAYERS))):
             cin, cout, dil = LAYERS[li]
-            dw = torch.empty_like(self.w[li])
-            db = torch.empty_like(self.b[li])
             dx = torch.empty_like(acts[li]) if li > 0 else None
             relu = li + 1 < len(LAYERS)
-            B.rks_net_conv3x3_backward(acts[li], self.w[li], acts[li + 1] if relu else None, g, dx, dw, db, Bn,
-                                       cin, cout, GRID, GRID, dil, relu)
-            gw[li], gb[li] = dw, db
+            B.rks_net_conv3x3_backward(acts[li], self.w[li], acts[li + 1] if relu else None, g, dx, gw[li],
+                                       gb[li], Bn, cin, cout, GRID, GRID, dil, relu)
             g = dx
         return gw, gb
 
@@ -116,7 +131,11 @@ class StartNet:
 
     def adam(self, gw, gb, lr):
         self.t += 1
-        for p, g, m, v in zip(self.w + self.b, gw + gb, self.m, self.v):
+        p, g = self.w + self.b, list(gw) + list(gb)
+        if all(_one_range(q, p) for q in (p, g, self.m, self.v)):
+            B.rks_net_adam(p[0], g[0], self.m[0], self.v[0], sum(q.numel() for q in p), lr, self.t)
+            return
+        for p, g, m, v in zip(p, g, self.m, self.v):  # entries that a caller replaced lie elsewhere
             B.rks_net_adam(p, g, m, v, p.numel(), lr, self.t)
 
     def predict(self, feats: np.ndarray):
@@ -143,8 +162,8 @@ class StartNet:
         net = cls(seed=0)
         with np.load(path, allow_pickle=False) as z:
             for i in range(len(LAYERS)):
-                net.w[i] = torch.tensor(z[f"w{i}"], dtype=torch.float32, device="cuda")
-                net.b[i] = torch.tensor(z[f"b{i}"], dtype=torch.float32, device="cuda")
+                net.w[i].copy_(torch.tensor(z[f"w{i}"], dtype=torch.float32))
+                net.b[i].copy_(torch.tensor(z[f"b{i}"], dtype=torch.float32))
         return net
 
 
