@@ -1217,14 +1217,31 @@ __device__ __forceinline__ void update_body(int64_t n, int64_t npk, int ncol, co
   bins_store(bins, spart, sp.d, sp.scale);
 }
 
+// One pass of classical Gram-Schmidt of deterministic Krylov-Schur: w - U y
+// with the coefficients formed by every workgroup in LDS from the products
+// yraw of the stored columns with the input (scaled by sc = *scale, or 1):
+// y_l = cs_l yraw_l sc, coef_l = cs_l y_l, coef_ncol = sc.  Workgroup 0 stores
+// h = y (first pass) or h += y.  (As launches of their own, one workgroup
+// each, the coefficients took 4.4 us per pass.)
 template <typename TV, typename TW, int KIND>
 __global__ __launch_bounds__(1024) void k_update(int64_t n, int64_t npk, int ncol, const TV* __restrict__ U,
                                                 int64_t ldu, const TW* __restrict__ w,
-                                                const double* __restrict__ coef, TV* __restrict__ unew,
-                                                double* __restrict__ spart, SketchP sp, int nkeep) {
-  extern __shared__ double bins[];  // 16 waves x d (none for KIND 3)
-  update_body<TV, TW, KIND>(n, npk, ncol, U, ldu, w, coef, unew, spart, sp, bins, nullptr, false, nullptr, nullptr,
-                            nullptr, nkeep);
+                                                const double* __restrict__ cs, const double* __restrict__ yraw,
+                                                const double* __restrict__ scale, double* __restrict__ h,
+                                                int accumulate, TV* __restrict__ unew, double* __restrict__ spart,
+                                                SketchP sp, int nkeep) {
+  extern __shared__ double smem[];  // the coefficients (kMaxM + 2), then 16 waves x d (none for KIND 3)
+  double* coef = smem;
+  const double sc = scale ? *scale : 1.0;
+  for (int l = threadIdx.x; l < ncol; l += blockDim.x) {
+    const double y = cs[l] * yraw[l] * sc;
+    coef[l] = cs[l] * y;
+    if (blockIdx.x == 0) h[l] = accumulate ? h[l] + y : y;
+  }
+  if (threadIdx.x == 0) coef[ncol] = sc;
+  __syncthreads();
+  update_body<TV, TW, KIND>(n, npk, ncol, U, ldu, w, coef, unew, spart, sp, smem + kMaxM + 2, nullptr, false, nullptr,
+                            nullptr, nullptr, nkeep);
 }
 
 // One randomized Arnoldi step's least squares and update in one launch: every
@@ -1358,35 +1375,39 @@ __global__ __launch_bounds__(1024) void k_dots(int64_t n, int64_t npk, int ncol,
   }
 }
 
-// Coefficients of one classical Gram-Schmidt pass from y_raw = sum of the
-// stored columns' products with the input (scaled by `scale`):
-// y_l = cs_l y_raw_l scale, coef_l = cs_l y_l, coef_ncol = scale; h += y.
-__global__ void k_ks_coef(int ncol, const double* __restrict__ cs, const double* __restrict__ yraw, double scale_in,
-                          const double* __restrict__ scale_ptr, double* __restrict__ coef, double* __restrict__ h,
-                          int accumulate) {
-  const double sc = scale_ptr ? *scale_ptr * scale_in : scale_in;
-  for (int l = threadIdx.x; l < ncol; l += blockDim.x) {
-    const double y = cs[l] * yraw[l] * sc;
-    coef[l] = cs[l] * y;
-    h[l] = accumulate ? h[l] + y : y;
+// Close step t of deterministic Krylov-Schur: the squared norm of u~ from its G
+// partial sums (in k_reduce's order), B(0:t, t) = h, B(t+1, t) = beta = ||u~||,
+// cs[t+1] = 1 / beta; breakdown test.  One workgroup.
+__global__ __launch_bounds__(1024) void k_ks_finalize(int t, const double* __restrict__ h,
+                                                     const double* __restrict__ part, int G, double* __restrict__ B,
+                                                     int ldb, double* __restrict__ cs, int* __restrict__ flags,
+                                                     double bd_rel) {
+  __shared__ double red[kRedSl];
+  const int sl = threadIdx.x;
+  if (sl < kRedSl) {
+    double a0 = 0.0, a1 = 0.0;
+    int g = sl;
+    for (; g + kRedSl < G; g += 2 * kRedSl) {
+      a0 += part[g];
+      a1 += part[g + kRedSl];
+    }
+    for (; g < G; g += kRedSl) a0 += part[g];
+    red[sl] = a0 + a1;
   }
-  if (threadIdx.x == 0) coef[ncol] = sc;
-}
-
-// Close step t of deterministic Krylov-Schur: B(0:t, t) = h, B(t+1, t) = beta
-// = ||u~|| (from the squared norm), cs[t+1] = 1 / beta; breakdown test.
-__global__ void k_ks_finalize(int t, const double* __restrict__ h, const double* __restrict__ nrm2, double* __restrict__ B,
-                              int ldb, double* __restrict__ cs, int* __restrict__ flags, double bd_rel) {
-  double hn = 0.0;
-  for (int l = threadIdx.x; l <= t; l += blockDim.x) {
-    B[l + (size_t)t * ldb] = h[l];
-  }
-  if (threadIdx.x == 0) {
-    for (int l = 0; l <= t; ++l) hn += h[l] * h[l];
-    const double beta = sqrt(*nrm2);
-    B[t + 1 + (size_t)t * ldb] = beta;
-    cs[t + 1] = 1.0 / beta;
-    if (!(beta > bd_rel * sqrt(hn + beta * beta)) && flags[0] == 0) flags[0] = t + 1;
+  for (int l = threadIdx.x; l <= t; l += blockDim.x) B[l + (size_t)t * ldb] = h[l];
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    double v = red[sl] + red[sl + 64];
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) v += __shfl_down(v, s);
+    if (threadIdx.x == 0) {
+      double hn = 0.0;
+      for (int l = 0; l <= t; ++l) hn += h[l] * h[l];
+      const double beta = sqrt(v);
+      B[t + 1 + (size_t)t * ldb] = beta;
+      cs[t + 1] = 1.0 / beta;
+      if (!(beta > bd_rel * sqrt(hn + beta * beta)) && flags[0] == 0) flags[0] = t + 1;
+    }
   }
 }
 
@@ -2215,32 +2236,14 @@ static int kept_columns(const LaunchEnv& e, int ncol) {
   return (int)(160e6 / col) & ~7;
 }
 
-int launch_update(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, const void* w, const double* coef,
-                  void* unew, double* spart) {
-  const int V = 16 / e.vbytes();
-  const int64_t npk = (e.n + V - 1) / V;
+int launch_update(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, const void* w, const double* cs,
+                  const double* yraw, const double* scale, double* h, int accumulate, void* unew, double* spart) {
+  const int64_t npk = (e.n + 1) / 2;
   const int G = grid_for(npk, 1024, kMaxG);
-  dim3 grid(G), block(1024);
-  const size_t lds = bins_lds(e, 16, e.sp_kind != 0);
-  const int nkeep = kept_columns(e, ncol);
-  if (e.prec == 0) {
-    RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_update<double, double, KIND>, lds);
-                      k_update<double, double, KIND><<<grid, block, lds, e.stream>>>(
-                          e.n, npk, ncol, (const double*)U, ldu, (const double*)w, coef, (double*)unew, spart, e.sp, nkeep));
-  } else if (e.prec == 1) {
-    RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_update<float, float, KIND>, lds);
-                      k_update<float, float, KIND><<<grid, block, lds, e.stream>>>(
-                          e.n, npk, ncol, (const float*)U, ldu, (const float*)w, coef, (float*)unew, spart, e.sp, nkeep));
-  } else {
-    RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_update<bf16_t, float, KIND>, lds);
-                      k_update<bf16_t, float, KIND><<<grid, block, lds, e.stream>>>(
-                          e.n, npk, ncol, (const bf16_t*)U, ldu, (const float*)w, coef, (bf16_t*)unew, spart, e.sp, nkeep));
-  }
-  if (e.sp_kind == 0) {  // sketch of the stored value
-    if (e.prec == 0) return gauss_t<double>(e, (const double*)unew, spart);
-    if (e.prec == 1) return gauss_t<float>(e, (const float*)unew, spart);
-    return gauss_t<bf16_t>(e, (const bf16_t*)unew, spart);
-  }
+  const size_t lds = ((size_t)kMaxM + 2) * 8 + bins_lds(e, 16, true);
+  k_update<double, double, 2><<<G, 1024, lds, e.stream>>>(e.n, npk, ncol, (const double*)U, ldu, (const double*)w, cs,
+                                                         yraw, scale, h, accumulate, (double*)unew, spart, e.sp,
+                                                         kept_columns(e, ncol));
   return G;
 }
 
@@ -2469,20 +2472,15 @@ void launch_reduce_len(const LaunchEnv& e, const double* pa, int Ga, double* oa,
   k_reduce<<<grid, block, 0, e.stream>>>(pa, nullptr, Ga, 0, len, oa, nullptr);
 }
 
-void launch_ks_coef(const LaunchEnv& e, int ncol, const double* cs, const double* yraw, double scale,
-                    const double* scale_ptr, double* coef, double* h, int accumulate) {
-  k_ks_coef<<<1, 256, 0, e.stream>>>(ncol, cs, yraw, scale, scale_ptr, coef, h, accumulate);
-}
-
 __global__ void k_ks_start(const double* __restrict__ nrm2, double* __restrict__ cs) {
   if (threadIdx.x == 0) cs[0] = 1.0 / sqrt(*nrm2);
 }
 
 void launch_ks_start(const LaunchEnv& e, const double* nrm2, double* cs) { k_ks_start<<<1, 64, 0, e.stream>>>(nrm2, cs); }
 
-void launch_ks_finalize(const LaunchEnv& e, int t, const double* h, const double* nrm2, double* B, int ldb, double* cs,
-                        int* flags, double bd_rel) {
-  k_ks_finalize<<<1, 256, 0, e.stream>>>(t, h, nrm2, B, ldb, cs, flags, bd_rel);
+void launch_ks_finalize(const LaunchEnv& e, int t, const double* h, const double* part, int G, double* B, int ldb,
+                        double* cs, int* flags, double bd_rel) {
+  k_ks_finalize<<<1, 1024, 0, e.stream>>>(t, h, part, G, B, ldb, cs, flags, bd_rel);
 }
 
 // ---------------------------------------------------------------------------

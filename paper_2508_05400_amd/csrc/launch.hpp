@@ -89,12 +89,13 @@ void launch_reduce(const LaunchEnv& e, const double* pa, int Ga, const double* p
 void launch_ls(const LaunchEnv& e, int t, int pending, int finalize_only, const double* zraw, const double* sraw,
                double* S, double* B, int ldb, double* E, double* cs, double* coef, double* scal, int* flags,
                double bd_rel);
-// (FP64, FP32 and BF16 bases: the deterministic Krylov-Schur step, which
-// takes no pair basis)
-int launch_update(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, const void* w, const double* coef,
-                  void* unew, double* spart);
-// Least squares (as launch_ls, not finalize-only) and update (as launch_update
-// with ncol = t + 1) in one launch; returns the number of partial rows.
+// One Gram-Schmidt pass of deterministic Krylov-Schur (FP64 basis): unew = sc w -
+// sum_l cs_l y_l U(:, l), y_l = cs_l yraw_l sc, sc = *scale (1 when null), h = y or,
+// when accumulate, h += y; partials of ||unew||^2 (returns their number).  w may be unew.
+int launch_update(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, const void* w, const double* cs,
+                  const double* yraw, const double* scale, double* h, int accumulate, void* unew, double* spart);
+// Least squares (as launch_ls, not finalize-only) and update (unew = w - U h over
+// the t + 1 columns, partials of its sketch) in one launch; returns the number of partial rows.
 int launch_ls_update(const LaunchEnv& e, int t, int pending, const double* zraw, const double* sraw, double* S,
                      double* B, int ldb, double* E, double* cs, double* coef, double* scal, int* flags,
                      double bd_rel, const void* U, int64_t ldu, const void* w, void* unew, double* spart);
@@ -123,13 +124,11 @@ void launch_copy16(hipStream_t stream, const void* src, void* dst, int64_t packe
 void launch_read16(hipStream_t stream, const void* src, int64_t packets);
 // Deterministic Krylov-Schur (Euclidean classical Gram-Schmidt, twice):
 // partials of U(:, 0:ncol)^T x (returns the number of partial rows), their sum,
-// the coefficients of one pass, and the closing of a step.
+// and the closing of a step from the G partials of its last pass.
 int launch_dots(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, const void* x, int x_is_basis, double* part);
 void launch_reduce_len(const LaunchEnv& e, const double* pa, int Ga, double* oa, int len);
-void launch_ks_coef(const LaunchEnv& e, int ncol, const double* cs, const double* yraw, double scale,
-                    const double* scale_ptr, double* coef, double* h, int accumulate);
-void launch_ks_finalize(const LaunchEnv& e, int t, const double* h, const double* nrm2, double* B, int ldb, double* cs,
-                        int* flags, double bd_rel);
+void launch_ks_finalize(const LaunchEnv& e, int t, const double* h, const double* part, int G, double* B, int ldb,
+                        double* cs, int* flags, double bd_rel);
 void launch_ks_start(const LaunchEnv& e, const double* nrm2, double* cs);
 // Device address of the library's fixed sketch scratch (kMaxG x kMaxD FP64)
 // on the current device, resolved once per device; 0 on success.

@@ -327,14 +327,11 @@ int arnoldi_step_ks(rks_ctx* c, int t) {
     Prof p(c, CAT_UPDATE, timed);
     int G = rks::launch_dots(e, ncol, c->U, c->ldu, c->w, 0, c->kpart);
     rks::launch_reduce_len(e, c->kpart, G, c->z, ncol);
-    rks::launch_ks_coef(e, ncol, c->cs, c->z, 1.0, c->cs + t, c->coef, c->sr, 0);
-    rks::launch_update(e, ncol, c->U, c->ldu, c->w, c->coef, unew, c->spart);
+    rks::launch_update(e, ncol, c->U, c->ldu, c->w, c->cs, c->z, c->cs + t, c->sr, 0, unew, c->spart);
     G = rks::launch_dots(e, ncol, c->U, c->ldu, unew, 1, c->kpart);
     rks::launch_reduce_len(e, c->kpart, G, c->z, ncol);
-    rks::launch_ks_coef(e, ncol, c->cs, c->z, 1.0, nullptr, c->coef, c->sr, 1);
-    const int Gs = rks::launch_update(e, ncol, c->U, c->ldu, unew, c->coef, unew, c->spart);
-    rks::launch_reduce_len(e, c->spart, Gs, c->scal + 2, 1);
-    rks::launch_ks_finalize(e, t, c->sr, c->scal + 2, c->B, c->m + 1, c->cs, c->flags, kBreakdownRel);
+    const int Gs = rks::launch_update(e, ncol, c->U, c->ldu, unew, c->cs, c->z, nullptr, c->sr, 1, unew, c->spart);
+    rks::launch_ks_finalize(e, t, c->sr, c->spart, Gs, c->B, c->m + 1, c->cs, c->flags, kBreakdownRel);
   }
   if (c->st) {
     const double bs = spmv_bytes(c), bu = (4.0 * (t + 1) + 6.0) * c->n * 8.0;
