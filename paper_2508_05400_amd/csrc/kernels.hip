@@ -1456,6 +1456,9 @@ __global__ __launch_bounds__(512) void k_init(int64_t n, TV* __restrict__ u, con
     for (; i < n; i += stride) {
       double v, g1;
       gauss_pair((uint64_t)i, c2, tag, s0, s1, v, g1);
+      // rounded to FP64 here: otherwise the pair's remainder x - hi is contracted
+      // with the product that v is, and splits the unrounded vector
+      asm("" : "+v"(v));
       row(i, v);
     }
   } else {
