@@ -2232,10 +2232,14 @@ void launch_ls(const LaunchEnv& e, int t, int pending, int finalize_only, const 
 // (m = 80) update 23.9 / 20.3, dots 34.2 / 24.2; on 10^6 rows 67.6 / 62.5 and
 // 63.1 / 61.4.  The rolling window keeps none: its columns are 13 MB or more,
 // and keeping 8 of them gained nothing (128^3, 2 10^6 rows) or cost the SpMV
-// more than it gained (160^3: 326 to 322, SpMV 49 to 53).
+// more than it gained (160^3: 326 to 322, SpMV 49 to 53).  A BF16 basis beyond
+// 320 MB keeps none either: its conversions, not HBM, bound the update (160^3:
+// 113 us without, 114 with 160 MB kept), and the SpMV's operands get the cache
+// (44 and 51 us; a bounded solve 96.9 and 98.0 ms, 128^3 55.7 and 55.8).
 static int kept_columns(const LaunchEnv& e, int ncol) {
   const double col = (double)e.n * (e.prec == 3 ? 6 : e.vbytes());
   if (ncol * col <= 320e6) return (ncol + 7) & ~7;
+  if (e.prec == 2) return 0;
   return (int)(160e6 / col) & ~7;
 }
 
