@@ -1963,14 +1963,16 @@ __global__ __launch_bounds__(256) void k_gauss_sketch(int64_t n, const TX* __res
     const double xv = HX && i < a1 ? Conv<TX>::ld(x[i]) : 0.0;
     const double yv = HY && i < a1 ? Conv<TY>::ld(y[i]) : 0.0;
     const int cnt = (int)min((int64_t)64, a1 - c);
-    auto add = [&](int j, double g0, double g1) {
+    // row c + j: x and y of it are read from lane j, which all lanes do (a lane
+    // without a pair holds values of the 64 rows, too)
+    auto row_x = [&](int j) { return HX ? readlane_f64(xv, j) : 0.0; };
+    auto row_y = [&](int j) { return HY ? readlane_f64(yv, j) : 0.0; };
+    auto add = [&](double v, double u, double g0, double g1) {
       if (HX) {
-        const double v = readlane_f64(xv, j);
         s0 += g0 * v;
         s1 += g1 * v;
       }
       if (HY) {
-        const double u = readlane_f64(yv, j);
         t0 += g0 * u;
         t1 += g1 * u;
       }
@@ -1984,15 +1986,17 @@ __global__ __launch_bounds__(256) void k_gauss_sketch(int64_t n, const TX* __res
         for (int j = 0; j < kGsU; ++j) g[j] = col[(int64_t)(j0 + j < cnt ? j0 + j : j0) * np];
 #pragma unroll
         for (int j = 0; j < kGsU; ++j)
-          if (j0 + j < cnt) add(j0 + j, g[j].x, g[j].y);
+          if (j0 + j < cnt) add(row_x(j0 + j), row_y(j0 + j), g[j].x, g[j].y);
       }
     } else {
-      for (int j = 0; j < cnt; ++j)
+      for (int j = 0; j < cnt; ++j) {
+        const double v = row_x(j), u = row_y(j);
         if (p < np) {
           double g0, g1;
           gauss_pair((uint64_t)(c + j), (uint32_t)p, 0u, sp.k0, sp.k1, g0, g1);
-          add(j, g0, g1);
+          add(v, u, g0, g1);
         }
+      }
     }
   }
   if (HX) {
