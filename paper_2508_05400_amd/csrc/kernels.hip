@@ -1781,7 +1781,8 @@ __global__ __launch_bounds__(256) void k_interleave(int64_t n, const double* __r
 // Any CSR matrix: 8 slots per wave, each with one lane per column of the
 // interleaved Xi, so that a gather is one 64-byte piece for all the columns
 // instead of a line for each.  A slot owns the rows that start in its equal
-// share of the nonzeros and walks their nonzeros as one sequence, kResidU
+// share of nonzeros and rows together (resid_row_at; by nonzeros alone, one
+// slot owns a whole run of empty rows) and walks their nonzeros as one sequence, kResidU
 // loads and gathers at a time, whatever the rows' lengths (one row per slot
 // with a common trip count waits for the longest of 8: 1.54 ms for 8 columns
 // of the 2M-row power-law operator against 0.92, 4.8 TB/s of 128-byte lines).  A row's products are added in
@@ -1804,19 +1805,9 @@ __global__ __launch_bounds__(256) void k_resid_csr(const int* __restrict__ rp, c
       kind = g.kind[q];
       im = kind == 1 ? g.im[q] : (kind == 2 ? -g.im[q] : 0.0);
     }
-  // the first row that starts at or after nonzero e
-  auto row_at = [&](int64_t e) {
-    int64_t lo = 0, hi = n;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (rp[mid] < e) lo = mid + 1;
-      else hi = mid;
-    }
-    return lo;
-  };
-  const int64_t share = (nnz + nslot - 1) / nslot;
-  int64_t r = row_at(min(nnz, slot * share));
-  const int64_t r1 = slot + 1 == nslot ? n : row_at(min(nnz, (slot + 1) * share));
+  const int64_t total = resid_key(nnz, n), share = (total + nslot - 1) / nslot;
+  int64_t r = resid_row_at(rp, n, min(total, slot * share));
+  const int64_t r1 = resid_row_at(rp, n, min(total, (slot + 1) * share));
   double rr = 0.0, xx = 0.0;
   if (r < r1) {
     int e = rp[r], rend = rp[r + 1], rnext = rp[r + 2 <= n ? r + 2 : n];

@@ -1,0 +1,69 @@
+"""Time and values of rks_eigpairs outside the sliced layout on matrices whose
+rows are shared unevenly: what one slot of the residual kernel walks must not
+set the time of the call."""
+import time
+
+import numpy as np
+import pytest
+import scipy.sparse as sp
+
+import paper_2508_05400_amd as P
+
+pytestmark = pytest.mark.gpu
+
+
+def _random_rows(n, seed, per=16):
+    rng = np.random.default_rng(seed)
+    cols = np.sort(rng.integers(0, n, (n, per)), axis=1) + np.arange(per)  # strictly increasing
+    cols = np.minimum(cols, n - per + np.arange(per))
+    return sp.csr_matrix((rng.standard_normal(n * per) / 4, cols.ravel(), np.arange(0, n * per + 1, per)), shape=(n, n))
+
+
+def _eigpairs(cuda, A, k, layout="rows"):
+    """Shortest of five calls in seconds, and what the last one returned."""
+    n, m = A.shape[0], 2 * k + 8
+    ctx = P.rks_create(A.indptr, A.indices, A.data, n, k, m, 2 * m + 3, "LM", 1e-10,
+                       P.rks_opts_default(sketch_seed=3, max_restarts=0, spmv_layout=layout, keep=-1))
+    try:
+        P.rks_solve(ctx)
+        ke = P.rks_num_pairs(ctx)
+        re, im, res = np.empty(ke), np.empty(ke), np.empty(ke)
+        X = cuda.empty((ke, n), dtype=cuda.float64, device="cuda")
+        ts = []
+        for _ in range(5):
+            cuda.cuda.synchronize()
+            t = time.perf_counter()
+            P.rks_eigpairs(ctx, re, im, X, res)
+            ts.append(time.perf_counter() - t)
+        return min(ts), re, im, X.cpu().numpy().T, res
+    finally:
+        P.rks_destroy(ctx)
+
+
+def _check(A, re, im, X, res):
+    """Residuals against NumPy: r and its terms as in test_gpu_resid.py, in norm."""
+    norm1, i = abs(A).sum(0).max(), 0
+    while i < len(re):
+        pair = im[i] != 0 and i + 1 < len(re)
+        x = X[:, i] + 1j * X[:, i + 1] if pair else X[:, i]
+        lam = re[i] + 1j * im[i] if pair else re[i]
+        r = np.linalg.norm(A @ x - lam * x) / norm1
+        L = np.diff(A.indptr).max()
+        bar = (L + 3) * 2.0**-53 * (np.linalg.norm(abs(A) @ abs(x)) + 2 * abs(lam)) / norm1 + len(x) * 2.0**-53 * r
+        assert abs(res[i] - r) <= 2 * bar
+        i += 2 if pair else 1
+
+
+@pytest.mark.parametrize("at", ["end", "middle"])
+def test_run_of_empty_rows(lib, cuda, at):
+    """60,000 empty rows of 120,000 in one run: walked by one slot they take
+    0.26 us each, 16 ms; with and without them the matrix has about the same
+    work (bar: 5 times the time without them, some 0.1 ms)."""
+    A = _random_rows(60000, 1)
+    h = 60000 if at == "end" else 30000
+    rp = np.concatenate([A.indptr[:h + 1], np.full(60000, A.indptr[h]), A.indptr[h + 1:]]).astype(np.int32)
+    B = sp.csr_matrix((A.data, A.indices, rp), shape=(120000, 120000))
+    t0 = _eigpairs(cuda, A, 7)[0]
+    t1, *out = _eigpairs(cuda, B, 7)
+    _check(B, *out)
+    assert t1 <= 5 * t0, (t0, t1)
