@@ -1868,6 +1868,32 @@ __global__ __launch_bounds__(256) void k_resid_csr(const int* __restrict__ rp, c
   }
 }
 
+// Up to kResidAx columns of a matrix outside the sliced layout: their products
+// with A were stored by the SpMV (AX, leading dimension n).  For so few columns
+// one SpMV each is faster than k_resid_csr, whose time hardly depends on their
+// number.  Measured, microseconds of rks_eigpairs with 2, 3 and 4 columns by
+// products / by k_resid_csr: 20,000 power-law rows 65, -, 90 / 102; 150,001 rows
+// 89, 112, 139 / 172; 2M rows in column blocks 595, 855, 1,117 / 1,035.
+__global__ __launch_bounds__(256) void k_resid_ax(int64_t n, const double* __restrict__ X,
+                                                  const double* __restrict__ AX, ResidGroup g,
+                                                  double* __restrict__ part, int ke) {
+  double rr[kResidV], xx[kResidV];
+#pragma unroll
+  for (int v = 0; v < kResidV; ++v) rr[v] = xx[v] = 0.0;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    double ax[kResidV], x[kResidV];
+#pragma unroll
+    for (int v = 0; v < kResidV; ++v) {
+      const bool in = v < kResidAx && v < g.nc;
+      ax[v] = in ? AX[(int64_t)v * n + i] : 0.0;
+      x[v] = in ? X[(int64_t)(g.first + v) * n + i] : 0.0;
+    }
+    resid_add(g, ax, x, rr, xx);
+  }
+  resid_store(g, rr, xx, part, ke);
+}
+
 // X(:, c) *= 1 / sqrt(sum of squares of its pair), sums as reduced from part.
 __global__ __launch_bounds__(256) void k_normalise(int64_t n, double* __restrict__ X, const double* __restrict__ sums,
                                                    PairKinds kinds) {
@@ -2438,6 +2464,9 @@ int launch_resid(const LaunchEnv& e, int64_t nnz, const double* X, int ke, const
     } else if (e.sl) {
       k_resid_sell<double><<<G, 256, 0, e.stream>>>(e.rp, e.sl_off, e.nsl, e.col_sl, e.val_sl, nullptr, e.n, X, g,
                                                     part, ke, e.sl_pad0);
+    } else if (g.nc <= (e.cb ? kResidAx - 1 : kResidAx)) {
+      for (int v = 0; v < g.nc; ++v) launch_spmv_sketch(e, X + (g.first + v) * e.n, Xi + v * e.n, nullptr, 0, 0);
+      k_resid_ax<<<G, 256, 0, e.stream>>>(e.n, X, Xi, g, part, ke);
     } else {
       k_interleave<<<grid_for(e.n, 256, 4096), 256, 0, e.stream>>>(e.n, X, g.first, g.nc, Xi);
       k_resid_csr<<<G, 256, 0, e.stream>>>(e.rp, e.col, e.val, e.n, nnz, Xi, g, part, ke);
