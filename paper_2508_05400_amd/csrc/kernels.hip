@@ -1868,12 +1868,8 @@ __global__ __launch_bounds__(256) void k_resid_csr(const int* __restrict__ rp, c
   }
 }
 
-// Up to kResidAx columns of a matrix outside the sliced layout: their products
-// with A were stored by the SpMV (AX, leading dimension n).  For so few columns
-// one SpMV each is faster than k_resid_csr, whose time hardly depends on their
-// number.  Measured, microseconds of rks_eigpairs with 2, 3 and 4 columns by
-// products / by k_resid_csr: 20,000 power-law rows 65, -, 90 / 102; 150,001 rows
-// 89, 112, 139 / 172; 2M rows in column blocks 595, 855, 1,117 / 1,035.
+// Columns of a matrix outside the sliced layout whose products with A were
+// stored by the SpMV (AX, leading dimension n); see resid_by_products.
 __global__ __launch_bounds__(256) void k_resid_ax(int64_t n, const double* __restrict__ X,
                                                   const double* __restrict__ AX, ResidGroup g,
                                                   double* __restrict__ part, int ke) {
@@ -1885,7 +1881,7 @@ __global__ __launch_bounds__(256) void k_resid_ax(int64_t n, const double* __res
     double ax[kResidV], x[kResidV];
 #pragma unroll
     for (int v = 0; v < kResidV; ++v) {
-      const bool in = v < kResidAx && v < g.nc;
+      const bool in = v < g.nc;
       ax[v] = in ? AX[(int64_t)v * n + i] : 0.0;
       x[v] = in ? X[(int64_t)(g.first + v) * n + i] : 0.0;
     }
@@ -2444,6 +2440,21 @@ void launch_rotate(const LaunchEnv& e, const void* U, int64_t ldu, int in0, int 
   }
 }
 
+// Whether nc columns outside the sliced layout take one SpMV each and a pass
+// over the products, instead of one walk of A for all of them (k_resid_csr).
+// Few columns do: the walk's time hardly depends on their number.  Measured,
+// microseconds of rks_eigpairs with 2, 3 and 4 columns by products / by a
+// walk: 20,000 power-law rows 57, -, 82 / 102; 150,001 rows 85, 110, 137 / 172;
+// 2M rows in column blocks 594, 844, 1,117 / 1,035.  So do matrices with a row
+// that one slot walks (0.11 us a nonzero) longer than the walk of all the
+// others takes; the SpMV gives such a row a whole wave.  7 columns
+// and one row of L nonzeros among power-law rows, by products / by a walk:
+// 150,001 rows, L = 1,200 - / 240, L = 2,400 232 / 381, L = 150,000 5,530 /
+// 16,900; 2M rows, L = 5,000 - / 1,281, L = 80,000 7,940 / 10,100.
+static bool resid_by_products(const LaunchEnv& e, int64_t nnz, int nc) {
+  return nc <= (e.cb ? 3 : 4) || e.longest > kTileFill + nnz / 2048;
+}
+
 int launch_resid(const LaunchEnv& e, int64_t nnz, const double* X, int ke, const int* kind, const double* re,
                  const double* im, double* Xi, double* part) {
   // (a multiple of 8: the slices are dealt to the XCDs)
@@ -2464,7 +2475,7 @@ int launch_resid(const LaunchEnv& e, int64_t nnz, const double* X, int ke, const
     } else if (e.sl) {
       k_resid_sell<double><<<G, 256, 0, e.stream>>>(e.rp, e.sl_off, e.nsl, e.col_sl, e.val_sl, nullptr, e.n, X, g,
                                                     part, ke, e.sl_pad0);
-    } else if (g.nc <= (e.cb ? kResidAx - 1 : kResidAx)) {
+    } else if (resid_by_products(e, nnz, g.nc)) {
       for (int v = 0; v < g.nc; ++v) launch_spmv_sketch(e, X + (g.first + v) * e.n, Xi + v * e.n, nullptr, 0, 0);
       k_resid_ax<<<G, 256, 0, e.stream>>>(e.n, X, Xi, g, part, ke);
     } else {

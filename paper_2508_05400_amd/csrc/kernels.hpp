@@ -63,7 +63,6 @@ struct Conv<bf16_t> {
 // columns first .. first + nc - 1 of X, of kind 0 (real), 1 and 2 (real and
 // imaginary part of a complex pair, both in the group), their eigenvalues.
 constexpr int kResidV = 8;
-constexpr int kResidAx = 4;  // columns at most whose products with A are stored (see k_resid_ax)
 constexpr int kResidMaxG = 2048;  // workgroups, and partial rows, at most
 struct ResidGroup {
   int first, nc;

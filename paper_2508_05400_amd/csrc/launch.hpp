@@ -13,6 +13,7 @@ struct LaunchEnv {
   int64_t n;
   int prec;            // 0 FP64 basis, 1 FP32 basis, 2 BF16 basis, 3 pair basis (FP32 + 16-bit remainder)
   const int* rp;       // CSR row pointers (device)
+  int longest = 0;     // nonzeros of the longest row
   const int* col;      // CSR columns (device)
   const double* val;   // FP64 values (device)
   const float* val32;  // FP32 values (device, mixed precision only)

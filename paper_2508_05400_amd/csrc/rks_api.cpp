@@ -1419,6 +1419,7 @@ int rks_create(const rks_csr* A, int32_t k, int32_t m, int32_t d, int32_t which,
     e.xcur = c->xcur;
   }
   e.rp = c->rp;
+  for (int64_t r = 0; r < n; ++r) e.longest = std::max(e.longest, rp[r + 1] - rp[r]);
   e.col = c->col;
   e.val = c->val;
   e.val32 = c->val32;

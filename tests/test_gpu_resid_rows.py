@@ -81,3 +81,24 @@ def test_few_columns(lib, cuda, k, layout):
     if k == 1 and layout == "rows":
         t8 = _eigpairs(cuda, A, 7, layout)[0]
         assert t1 <= 0.75 * t8, (t1, t8)
+
+
+def test_one_long_row(lib, cuda):
+    """A row of 100,000 nonzeros is added by a wave, not by one slot: eight
+    residuals take no more than eight products with A (bar: 1.5 of them and
+    0.3 ms; by one slot they take 2.5)."""
+    A = _random_rows(100000, 3).tolil()
+    A[33333, :] = np.random.default_rng(4).standard_normal(100000) / 300
+    A = A.tocsr()
+    t8, *out = _eigpairs(cuda, A, 7)
+    _check(A, *out)
+    ctx = P.rks_create(A.indptr, A.indices, A.data, 100000, 2, 10, 20, "LM", 1e-10,
+                       P.rks_opts_default(spmv_layout="rows"))
+    x, w, z = (cuda.ones(s, dtype=cuda.float64, device="cuda") for s in (100000, 100000, 20))
+    ts = []
+    for _ in range(5):
+        t = time.perf_counter()
+        P.rks_spmv_sketch(ctx, x, w, z)  # returns when done
+        ts.append(time.perf_counter() - t)
+    P.rks_destroy(ctx)
+    assert t8 <= 1.5 * 8 * min(ts) + 3e-4, (t8, min(ts))
