@@ -1831,12 +1831,12 @@ __global__ __launch_bounds__(256) void k_resid_csr(const int* __restrict__ rp, c
       }
     };
     finish(e);  // leading empty rows
-    for (; e < et; e += kResidU) {
+    for (; e < et; e = batch_next(e, kResidU, et)) {
       double a[kResidU], xv[kResidU];
       int c[kResidU];
 #pragma unroll
       for (int q = 0; q < kResidU; ++q) {
-        const int eq = e + q < et ? e + q : e;
+        const int eq = batch_entry(e, q, et);
         c[q] = col[eq];
         a[q] = val[eq];
       }
@@ -1844,7 +1844,7 @@ __global__ __launch_bounds__(256) void k_resid_csr(const int* __restrict__ rp, c
       for (int q = 0; q < kResidU; ++q) xv[q] = Xi[(int64_t)c[q] * kResidV + v];
 #pragma unroll
       for (int q = 0; q < kResidU; ++q)
-        if (e + q < et) {
+        if (q < et - e) {
           ax += a[q] * xv[q];
           finish(e + q + 1);
         }

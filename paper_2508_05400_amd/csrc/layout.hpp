@@ -50,4 +50,10 @@ constexpr int64_t resid_row_at(const int* rp, int64_t n, int64_t key) {
   return lo;
 }
 
+// Batches of u of the entries e .. et - 1, et up to 2^31 - 1: entry q of the
+// batch at e (past the end: e), and where the next batch starts (or et).  No
+// sum passes et.
+constexpr int batch_entry(int e, int q, int et) { return q < et - e ? e + q : e; }
+constexpr int batch_next(int e, int u, int et) { return et - e > u ? e + u : et; }
+
 }  // namespace rks

@@ -1,7 +1,8 @@
 // Host check of the split of a CSR matrix's rows among the slots of the
 // residual kernel (layout.hpp): every row once, in order, and no slot with more
-// work than its share and one row.
+// work than its share and one row; and of its batches of nonzeros.
 #include <algorithm>
+#include <climits>
 #include <cstdio>
 #include <random>
 #include <vector>
@@ -33,7 +34,21 @@ static void split(const std::vector<int>& rp, int64_t nslot) {
   CHECK(next == n);
 }
 
+// The last entries of the largest matrix: every entry once, none past the end.
+static void batches(int e0, int et, int u) {
+  int next = e0;
+  for (int e = e0; e < et; e = rks::batch_next(e, u, et))
+    for (int q = 0; q < u; ++q) {
+      const int eq = rks::batch_entry(e, q, et);
+      CHECK(eq >= e0 && eq < et);
+      if (q < et - e) CHECK(eq == next++);
+    }
+  CHECK(next == et);
+}
+
 int main() {
+  for (int len = 1; len < 40; ++len)
+    for (int et : {40, INT_MAX - 7, INT_MAX}) batches(et - len, et, 8);
   std::mt19937 g(7);
   for (int64_t n : {4, 64, 1031, 40000})
     for (int kind = 0; kind < 5; ++kind) {

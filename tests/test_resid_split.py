@@ -1,6 +1,6 @@
 """The split of a matrix's rows among the slots of the row-layout residual
 kernel, on the host under UBSan: runs of empty rows, no nonzeros, more slots
-than rows."""
+than rows; and its batches of nonzeros up to entry 2^31 - 2."""
 import os
 import shutil
 import subprocess
