@@ -1810,11 +1810,11 @@ __global__ __launch_bounds__(256) void k_resid_csr(const int* __restrict__ rp, c
   const int64_t r1 = resid_row_at(rp, n, min(total, (slot + 1) * share));
   double rr = 0.0, xx = 0.0;
   if (r < r1) {
-    int e = rp[r], rend = rp[r + 1], rnext = rp[r + 2 <= n ? r + 2 : n];
-    const int et = rp[r1];
+    uint32_t e = rp[r], rend = rp[r + 1], rnext = rp[r + 2 <= n ? r + 2 : n];
+    const uint32_t et = rp[r1];
     double x = Xi[r * kResidV + v], xn = Xi[(r + 1 < n ? r + 1 : r) * kResidV + v], ax = 0.0;
     // rows that end at nonzero e1: the current one, and empty ones behind it
-    auto finish = [&](int e1) {
+    auto finish = [&](uint32_t e1) {
       while (r < r1 && rend == e1) {
         const double p1 = __shfl_down(x, 1), p2 = __shfl_up(x, 1);
         double res = ax - re * x;
@@ -1831,12 +1831,12 @@ __global__ __launch_bounds__(256) void k_resid_csr(const int* __restrict__ rp, c
       }
     };
     finish(e);  // leading empty rows
-    for (; e < et; e = batch_next(e, kResidU, et)) {
+    for (; e < et; e += kResidU) {
       double a[kResidU], xv[kResidU];
       int c[kResidU];
 #pragma unroll
       for (int q = 0; q < kResidU; ++q) {
-        const int eq = batch_entry(e, q, et);
+        const uint32_t eq = batch_entry(e, q, et);
         c[q] = col[eq];
         a[q] = val[eq];
       }
@@ -1844,7 +1844,7 @@ __global__ __launch_bounds__(256) void k_resid_csr(const int* __restrict__ rp, c
       for (int q = 0; q < kResidU; ++q) xv[q] = Xi[(int64_t)c[q] * kResidV + v];
 #pragma unroll
       for (int q = 0; q < kResidU; ++q)
-        if (q < et - e) {
+        if (e + q < et) {
           ax += a[q] * xv[q];
           finish(e + q + 1);
         }

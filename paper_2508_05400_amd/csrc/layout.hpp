@@ -50,10 +50,9 @@ constexpr int64_t resid_row_at(const int* rp, int64_t n, int64_t key) {
   return lo;
 }
 
-// Batches of u of the entries e .. et - 1, et up to 2^31 - 1: entry q of the
-// batch at e (past the end: e), and where the next batch starts (or et).  No
-// sum passes et.
-constexpr int batch_entry(int e, int q, int et) { return q < et - e ? e + q : e; }
-constexpr int batch_next(int e, int u, int et) { return et - e > u ? e + u : et; }
+// Entry q of the batch of entries at e, e < et (past the end: e).  Unsigned: et
+// may be 2^31 - 1, past which e + q must not wrap (forming what is left of the
+// range in signed arithmetic instead took k_resid_csr 6% longer).
+constexpr uint32_t batch_entry(uint32_t e, uint32_t q, uint32_t et) { return e + q < et ? e + q : e; }
 
 }  // namespace rks

@@ -35,13 +35,13 @@ static void split(const std::vector<int>& rp, int64_t nslot) {
 }
 
 // The last entries of the largest matrix: every entry once, none past the end.
-static void batches(int e0, int et, int u) {
-  int next = e0;
-  for (int e = e0; e < et; e = rks::batch_next(e, u, et))
-    for (int q = 0; q < u; ++q) {
-      const int eq = rks::batch_entry(e, q, et);
+static void batches(uint32_t e0, uint32_t et, uint32_t u) {
+  uint32_t next = e0;
+  for (uint32_t e = e0; e < et; e += u)
+    for (uint32_t q = 0; q < u; ++q) {
+      const uint32_t eq = rks::batch_entry(e, q, et);
       CHECK(eq >= e0 && eq < et);
-      if (q < et - e) CHECK(eq == next++);
+      if (e + q < et) CHECK(eq == next++);
     }
   CHECK(next == et);
 }
