@@ -2451,18 +2451,20 @@ void launch_rotate(const LaunchEnv& e, const void* U, int64_t ldu, int in0, int 
 // and one row of L nonzeros among power-law rows, by products / by a walk:
 // 150,001 rows, L = 1,200 - / 240, L = 2,400 232 / 381, L = 150,000 5,530 /
 // 16,900; 2M rows, L = 5,000 - / 1,281, L = 80,000 7,940 / 10,100.
-static bool resid_by_products(const LaunchEnv& e, int64_t nnz, int nc) {
-  return nc <= (e.cb ? 3 : 4) || e.longest > kTileFill + nnz / 2048;
+// The walk also needs the whole scratch (kResidV columns).
+static bool resid_by_products(const LaunchEnv& e, int64_t nnz, int nc, int xcols) {
+  return nc <= (e.cb ? 3 : 4) || xcols < kResidV || e.longest > kTileFill + nnz / 2048;
 }
 
 int launch_resid(const LaunchEnv& e, int64_t nnz, const double* X, int ke, const int* kind, const double* re,
-                 const double* im, double* Xi, double* part) {
+                 const double* im, double* Xi, int xcols, double* part) {
+  const int gmax = e.sl ? kResidV : xcols;
   // (a multiple of 8: the slices are dealt to the XCDs)
   const int G = (grid_for(e.sl ? e.nsl : (std::max(nnz, 64 * e.n / 8) + 511) / 512, 4, kResidMaxG) + 7) & ~7;
   for (int c = 0; c < ke;) {
     ResidGroup g{};
     g.first = c;
-    while (c < ke && g.nc < kResidV && !(kind[c] == 1 && g.nc + 1 == kResidV)) {  // a complex pair stays together
+    while (c < ke && g.nc < gmax && !(kind[c] == 1 && g.nc + 1 == gmax)) {  // a complex pair stays together
       g.kind[g.nc] = kind[c];
       g.re[g.nc] = re[c];
       g.im[g.nc] = kind[c] == 2 ? im[c - 1] : im[c];
@@ -2475,7 +2477,7 @@ int launch_resid(const LaunchEnv& e, int64_t nnz, const double* X, int ke, const
     } else if (e.sl) {
       k_resid_sell<double><<<G, 256, 0, e.stream>>>(e.rp, e.sl_off, e.nsl, e.col_sl, e.val_sl, nullptr, e.n, X, g,
                                                     part, ke, e.sl_pad0);
-    } else if (resid_by_products(e, nnz, g.nc)) {
+    } else if (resid_by_products(e, nnz, g.nc, xcols)) {
       for (int v = 0; v < g.nc; ++v) launch_spmv_sketch(e, X + (g.first + v) * e.n, Xi + v * e.n, nullptr, 0, 0);
       k_resid_ax<<<G, 256, 0, e.stream>>>(e.n, X, Xi, g, part, ke);
     } else {

@@ -115,9 +115,10 @@ void launch_rotate(const LaunchEnv& e, const void* U, int64_t ldu, int in0, int 
 // (2 ke per row: of column c at 2 c and 2 c + 1); returns the number of rows
 // (at most kResidMaxG).  kind: 0 a real pair, 1 and 2 the real and the imaginary
 // part of a complex one, whose eigenvalue is read at the first.  Xi: scratch
-// of n kResidV values (interleaved columns, or products with A), unused in the sliced layout.
+// of n xcols values (interleaved columns, or products with A; xcols = kResidV,
+// or 2 for columns in groups of two), unused in the sliced layout.
 int launch_resid(const LaunchEnv& e, int64_t nnz, const double* X, int ke, const int* kind, const double* re,
-                 const double* im, double* Xi, double* part);
+                 const double* im, double* Xi, int xcols, double* part);
 // Scales every pair of X to unit norm, sums being the sums of launch_resid's rows.
 void launch_normalise(const LaunchEnv& e, double* X, int ke, const int* kind, const double* sums);
 void launch_fill(const LaunchEnv& e, int64_t len, double* x, double v);

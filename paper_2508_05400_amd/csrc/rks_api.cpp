@@ -96,6 +96,7 @@ struct rks_ctx {
   double* val_pn = nullptr;
   float* val32_pn = nullptr;
   double *Xr = nullptr, *Xi = nullptr, *rpart = nullptr;  // residual scratch (lazy)
+  int Xi_cols = 0;                                        // columns of Xi: kResidV, or 2
   // E, B, S, cs and flags live in one device block and one pinned host block
   // of the same layout, so a restart moves them with one copy each way
   void* dstate = nullptr;
@@ -149,6 +150,28 @@ int fail(rks_ctx* c, int code, const std::string& msg) {
     hipError_t e_ = (call);                                                                      \
     if (e_ != hipSuccess) return fail((ctx), RKS_EHIP, std::string(#call) + " -> " + hipGetErrorString(e_)); \
   } while (0)
+
+// hipMalloc that leaves a null pointer and no error behind when it fails.
+bool try_malloc(void** p, size_t bytes) {
+  if (hipMalloc(p, bytes) == hipSuccess) return true;
+  *p = nullptr;
+  (void)hipGetLastError();
+  return false;
+}
+
+// Memory of a buffer that is allocated on first use.  When there is none left,
+// buffers that the context can do with less of are given back first: the wide
+// scratch of the residuals.
+bool late_malloc(rks_ctx* c, void** p, size_t bytes) {
+  if (try_malloc(p, bytes)) return true;
+  (void)hipStreamSynchronize(c->env.stream);
+  if (c->Xi && c->Xi_cols > 2) {
+    (void)hipFree(c->Xi);
+    c->Xi = nullptr;
+    if (try_malloc(p, bytes)) return true;
+  }
+  return false;
+}
 
 void* basis_col(rks_ctx* c, int l) { return (char*)c->U + (size_t)l * c->ldu * c->vbytes; }
 
@@ -831,13 +854,19 @@ Packed pack_ritz(const rks_ctx* c) {
 }
 
 int ensure_resid_scratch(rks_ctx* c) {
-  const size_t cols = (size_t)c->k + 1;
-  if (!c->Xr && hipMalloc(&c->Xr, (size_t)c->n * cols * 8) != hipSuccess) return fail(c, RKS_ENOMEM, "residual X");
-  if (!c->Xi && !c->env.sl && hipMalloc(&c->Xi, (size_t)c->n * rks::kResidV * 8) != hipSuccess)
-    return fail(c, RKS_ENOMEM, "residual X, interleaved");
+  const size_t cols = (size_t)c->k + 1, col = (size_t)c->n * 8;
+  if (!c->Xr && !late_malloc(c, (void**)&c->Xr, col * cols)) return fail(c, RKS_ENOMEM, "residual X");
   // partial rows, then their sums
-  if (!c->rpart && hipMalloc(&c->rpart, cols * 2 * (rks::kResidMaxG + 1) * 8) != hipSuccess)
+  if (!c->rpart && !late_malloc(c, (void**)&c->rpart, cols * 2 * (rks::kResidMaxG + 1) * 8))
     return fail(c, RKS_ENOMEM, "residual partials");
+  if (!c->Xi && !c->env.sl) {
+    // kResidV columns, or two where there is no room for them (slower, the same residuals)
+    c->Xi_cols = rks::kResidV;
+    if (!try_malloc((void**)&c->Xi, col * c->Xi_cols)) {
+      c->Xi_cols = 2;
+      if (!late_malloc(c, (void**)&c->Xi, col * c->Xi_cols)) return fail(c, RKS_ENOMEM, "residual products");
+    }
+  }
   return RKS_OK;
 }
 
@@ -858,7 +887,8 @@ int device_residuals(rks_ctx* c, const Packed& P, double* Xd, double* resid, boo
     if (P.pair_of[i] == 2) re[i] = re[i - 1];
   }
   double* sums = c->rpart + (size_t)rks::kResidMaxG * 2 * ke;
-  const int G = rks::launch_resid(c->env, c->nnz, Xd, ke, P.pair_of.data(), re.data(), im.data(), c->Xi, c->rpart);
+  const int G = rks::launch_resid(c->env, c->nnz, Xd, ke, P.pair_of.data(), re.data(), im.data(), c->Xi,
+                                  c->Xi_cols, c->rpart);
   rks::launch_reduce_len(c->env, c->rpart, G, sums, 2 * ke);
   if (normalise) rks::launch_normalise(c->env, Xd, ke, P.pair_of.data(), sums);
   HIPCHK(c, hipGetLastError());
@@ -907,10 +937,7 @@ int set_basis(rks_ctx* c, int prec) {
   } else {
     if (!c->U64) {
       const size_t bytes = (size_t)c->ldu * (c->m + 1) * 8;
-      if (hipMalloc(&c->U64, bytes) != hipSuccess) {
-        c->U64 = nullptr;
-        return fail(c, RKS_ENOMEM, "FP64 refinement basis");
-      }
+      if (!late_malloc(c, &c->U64, bytes)) return fail(c, RKS_ENOMEM, "FP64 refinement basis");
       HIPCHK(c, hipMemsetAsync(c->U64, 0, bytes, c->env.stream));
     }
     c->U = c->U64;
