@@ -160,8 +160,9 @@ bool try_malloc(void** p, size_t bytes) {
 }
 
 // Memory of a buffer that is allocated on first use.  When there is none left,
-// buffers that the context can do with less of are given back first: the wide
-// scratch of the residuals.
+// what the context can do without is given back first: the wide scratch of the
+// residuals, then the stored Omega (evaluated from then on, with the same
+// results to the bit) with the recorded graphs, whose launches read it.
 bool late_malloc(rks_ctx* c, void** p, size_t bytes) {
   if (try_malloc(p, bytes)) return true;
   (void)hipStreamSynchronize(c->env.stream);
@@ -170,7 +171,13 @@ bool late_malloc(rks_ctx* c, void** p, size_t bytes) {
     c->Xi = nullptr;
     if (try_malloc(p, bytes)) return true;
   }
-  return false;
+  if (!c->om) return false;
+  for (auto& kv : c->gexec) (void)hipGraphExecDestroy(kv.second);
+  c->gexec.clear();
+  (void)hipFree(c->om);
+  c->om = nullptr;
+  c->env.om = nullptr;
+  return try_malloc(p, bytes);
 }
 
 void* basis_col(rks_ctx* c, int l) { return (char*)c->U + (size_t)l * c->ldu * c->vbytes; }

@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <vector>
 
@@ -65,10 +66,8 @@ hipError_t hipEventElapsedTime(float*, hipEvent_t, hipEvent_t) { return hipError
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)&live; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 
-// A recorded graph is the list of buffers that its launches were given.
-struct Graph {
-  std::vector<const void*> used;
-};
+// A recorded graph is the list of what its launches do.
+typedef std::vector<std::function<void()>> Graph;
 static Graph* recording = nullptr;
 static int replays = 0;
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { recording = new Graph; return hipSuccess; }
@@ -80,26 +79,35 @@ hipError_t hipGraphInstantiate(hipGraphExec_t* x, hipGraph_t g, hipGraphNode_t*,
 hipError_t hipGraphDestroy(hipGraph_t g) { delete (Graph*)g; return hipSuccess; }
 hipError_t hipGraphExecDestroy(hipGraphExec_t x) { delete (Graph*)x; return hipSuccess; }
 hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t) {
-  for (const void* p : ((Graph*)x)->used) CHECK(allocated(p));
+  for (auto& f : *(Graph*)x) f();
   ++replays;
   return hipSuccess;
 }
 }  // extern "C"
 
+static void run(std::function<void()> f) {
+  if (recording) recording->push_back(f);
+  else f();
+}
 static void use(const void* p, size_t bytes = 1) {
-  if (!p) return;
-  CHECK(allocated(p, bytes));
-  if (recording) recording->used.push_back(p);
+  if (p) run([=] { CHECK(allocated(p, bytes)); });
 }
 
 // ---- the launchers ---------------------------------------------------------------
 static int resid_cols = 0;  // scratch columns of the last residual launch
+static int stored = 0, evaluated = 0;  // Gaussian sketches
 namespace rks {
 int launch_spmv_sketch(const LaunchEnv& e, const void* x, void* w, double*, int, int) { use(x); use(w); return 1; }
-int launch_gauss(const LaunchEnv& e, const void*, const void*, double*, double*) { use(e.om); return 1; }
+int launch_gauss(const LaunchEnv& e, const void*, const void*, double*, double*) {
+  use(e.om);
+  run([om = e.om] { (om ? stored : evaluated) += 1; });
+  return 1;
+}
 void launch_omega_fill(const LaunchEnv& e, double* om) { use(om, (size_t)(e.sp.d + 1) / 2 * e.n * 16); }
 void launch_reduce(const LaunchEnv&, const double*, int, const double*, int, double*, double*) {}
-static void column(const LaunchEnv& e, int t, double* S, double* cs) { S[t + (size_t)t * e.sp.d] = cs[t] = 1.0; }
+static void column(const LaunchEnv& e, int t, double* S, double* cs) {
+  run([=, d = e.sp.d] { S[t + (size_t)t * d] = cs[t] = 1.0; });
+}
 void launch_ls(const LaunchEnv& e, int t, int, int, const double*, const double*, double* S, double*, int, double*, double* cs, double*, double*, int*, double) { column(e, t, S, cs); }
 int launch_update(const LaunchEnv&, int, const void*, int64_t, const void*, const double*, const double*, const double*, double*, int, void*, double*) { return 1; }
 int launch_ls_update(const LaunchEnv& e, int t, int, const double*, const double*, double* S, double* B, int ldb, double*, double* cs, double*, double*, int*, double, const void* U, int64_t, const void* w, void* u, double*) {
@@ -107,9 +115,11 @@ int launch_ls_update(const LaunchEnv& e, int t, int, const double*, const double
   use(w);
   use(u);
   column(e, t, S, cs);
-  static int calls = 0;
-  B[t + (size_t)t * ldb] = 1.0 + 0.01 * ++calls;
-  B[t + 1 + (size_t)t * ldb] = 0.001;
+  run([=] {
+    static int calls = 0;
+    B[t + (size_t)t * ldb] = 1.0 + 0.01 * ++calls;
+    B[t + 1 + (size_t)t * ldb] = 0.001;
+  });
   return 1;
 }
 int launch_init(const LaunchEnv&, void* u, const double*, uint32_t, uint32_t, double*, int, int, uint32_t, uint32_t) { use(u); return 1; }
@@ -182,8 +192,39 @@ static void residual_scratch() {
   CHECK(live.empty());
 }
 
+static void gauss(rks_opts* o) {
+  o->sketch_kind = RKS_SKETCH_GAUSS;
+  o->graphs = 1;
+}
+
+// A stored Omega gives way to what a context allocates at its first use.
+static void stored_omega() {
+  rks_ctx* c = context(gauss);
+  CHECK(rks_solve(c, nullptr, 0, nullptr) == RKS_ENOTCONV);
+  CHECK(rks_solve(c, nullptr, 0, nullptr) == RKS_ENOTCONV && replays > 0);
+  CHECK(stored > 0 && evaluated == 0);
+  room = xr - 8;
+  CHECK(eigpairs(c) == RKS_OK);
+  stored = 0;
+  CHECK(rks_solve(c, nullptr, 0, nullptr) == RKS_ENOTCONV && eigpairs(c) == RKS_OK);  // no graph reads it
+  CHECK(stored == 0 && evaluated > 0);
+  room = (size_t)1 << 40;
+  rks_destroy(c);
+  CHECK(live.empty());
+  // in the middle of a solve: the FP64 basis of the refinement
+  evaluated = 0;
+  c = context([](rks_opts* o) { gauss(o); o->precision = RKS_PREC_V32; });
+  room = xr + rpart + u64 - 8;
+  CHECK(rks_solve(c, nullptr, 0, nullptr) == RKS_ENOTCONV && evaluated > 0);
+  CHECK(eigpairs(c) == RKS_OK);
+  room = (size_t)1 << 40;
+  rks_destroy(c);
+  CHECK(live.empty());
+}
+
 int main() {
   residual_scratch();
+  stored_omega();
   std::printf("ok: %d failures\n", failures);
   return failures != 0;
 }
