@@ -50,10 +50,15 @@ typedef enum { RKS_LM = 0, RKS_SM = 1, RKS_LR = 2, RKS_SR = 3 } rks_which;
  *            (Section 5 uses zeta = 8).
  * Omega's entries are a function of Philox4x32-10 counters (column index,
  * slot) keyed by sketch_seed.  A sparse Omega is regenerated by every kernel
- * that needs it; a context stores a Gaussian one of up to 4 GiB (8 n d bytes)
- * and regenerates a larger one, or one the device has no room for, with the
- * same results to the bit. */
+ * that needs it; a Gaussian one may be stored (rks_omega). */
 typedef enum { RKS_SKETCH_GAUSS = 0, RKS_SKETCH_SPARSE = 1 } rks_sketch_kind;
+
+/* A context's Gaussian Omega.  AUTO: stored in device memory (8 n d bytes) if
+ * it takes at most 4 GiB and at most 1/32 of the memory that is free when the
+ * context is created; given back when a later allocation of the context needs
+ * its room.  EVALUATE: never stored, its entries are formed by every kernel
+ * that needs them.  The results are the same to the bit. */
+typedef enum { RKS_OMEGA_AUTO = 0, RKS_OMEGA_EVALUATE = 1 } rks_omega;
 
 /* Storage precision of the n-dimensional basis U (mixed precision is the
  * paper's future-work direction of Section 6; sketch-space quantities, the
@@ -186,6 +191,7 @@ typedef struct {
   int32_t a_values;      /* rks_a_values: storage of A's values for the FP64 product,
                             default AUTO (value-indexed when A has at most 256
                             distinct values) */
+  int32_t omega;         /* rks_omega: storage of a Gaussian embedding, default AUTO */
 } rks_opts;
 
 /* Fills *o with the defaults listed above. */
@@ -239,8 +245,8 @@ typedef struct {
  * rotation writes at most 128 columns), tol > 0, a valid CSR.  opts may be
  * NULL (defaults).
  * Allocates the basis U (n x (m+1)), the sketch S (d x (m+1)), the Rayleigh
- * quotient B ((m+1) x m) and scratch on the device, and a Gaussian Omega of
- * up to 4 GiB.
+ * quotient B ((m+1) x m) and scratch on the device, and a Gaussian Omega
+ * (rks_opts.omega).
  * Errors: RKS_EINVAL, RKS_ENAN (non-finite value in A), RKS_ENOMEM, RKS_EHIP. */
 int rks_create(const rks_csr* A, int32_t k, int32_t m, int32_t d, int32_t which, double tol,
                const rks_opts* opts, struct rks_ctx** out);

@@ -20,6 +20,7 @@ PRECISION = {"fp64": 0, "fp32": 1, "v32": 1, "bf16": 2, "vbf16": 2, "fp32+fx16":
 SPMV_LAYOUT = {"auto": 0, "rows": 1, "column_blocks": 2, "sliced": 3}
 METHOD = {"rks": 0, "ks_cgs2": 1}
 A_VALUES = {"auto": 0, "fp64": 1}
+OMEGA = {"auto": 0, "evaluate": 1}
 
 
 class RksCsr(ctypes.Structure):
@@ -36,7 +37,7 @@ class RksOpts(ctypes.Structure):
                 ("resid_tol", ctypes.c_double), ("refine", ctypes.c_int32),
                 ("refine_tol", ctypes.c_double), ("spmv_layout", ctypes.c_int32),
                 ("method", ctypes.c_int32), ("keep", ctypes.c_int32), ("graphs", ctypes.c_int32),
-                ("stall_restarts", ctypes.c_int32), ("a_values", ctypes.c_int32)]
+                ("stall_restarts", ctypes.c_int32), ("a_values", ctypes.c_int32), ("omega", ctypes.c_int32)]
 
 
 class RksStats(ctypes.Structure):
@@ -171,6 +172,8 @@ def rks_opts_default(**kw) -> RksOpts:
             v = METHOD[v]
         if k == "a_values" and isinstance(v, str):
             v = A_VALUES[v]
+        if k == "omega" and isinstance(v, str):
+            v = OMEGA[v]
         if k == "stream" and v is not None and not isinstance(v, int):
             v = int(v.cuda_stream)
         setattr(o, k, v)

@@ -25,7 +25,11 @@ constexpr int kMaxM = 255;       // largest Krylov dimension
 constexpr int kMaxG = 512;       // largest number of partial-sum rows (producer blocks)
 constexpr int kMaxPart0 = kSpmvMaxG > kMaxG ? kSpmvMaxG : kMaxG;
 constexpr int kMaxPart = kSellMaxG > kMaxPart0 ? kSellMaxG : kMaxPart0;  // partial rows of the row-tile or sliced SpMV's sketch
-constexpr size_t kOmegaMax = (size_t)4 << 30;  // a context stores a Gaussian Omega up to this size
+// A context stores a Gaussian Omega of up to kOmegaMax bytes and 1/kOmegaShare
+// of the free memory: contexts that fill the device keep most of it for their
+// bases, and on an empty one (288 GB) every Omega of kOmegaMax is stored.
+constexpr size_t kOmegaMax = (size_t)4 << 30;
+constexpr size_t kOmegaShare = 32;
 constexpr int kRotMax = 128;     // output columns per rotation pass (8 MFMA column tiles)
 constexpr size_t kRotLdsMax = 160 * 1024;  // Y in LDS up to this size, else read from global memory
 constexpr size_t kLsLdsMax = 150 * 1024;  // LDS budget of the least-squares kernel

@@ -1144,10 +1144,11 @@ int rks_create(const rks_csr* A, int32_t k, int32_t m, int32_t d, int32_t which,
     return fail(nullptr, RKS_EINVAL, "need 1 <= zeta <= min(8, d)");
   if (o.precision < 0 || o.precision > 3 || o.max_restarts < 0 || !(o.whiten_tol >= 0.0) ||
       !(o.resid_tol >= 0.0) || !(o.refine_tol >= 0.0) || o.spmv_layout < 0 || o.spmv_layout > 3 || o.method < 0 ||
-      o.method > 1 || o.graphs < 0 || o.graphs > 1 || o.stall_restarts < 0 || o.a_values < 0 || o.a_values > 1)
+      o.method > 1 || o.graphs < 0 || o.graphs > 1 || o.stall_restarts < 0 || o.a_values < 0 || o.a_values > 1 ||
+      o.omega < 0 || o.omega > 1)
     return fail(nullptr, RKS_EINVAL,
                 "precision, max_restarts, whiten_tol, resid_tol, refine_tol, spmv_layout, method, graphs, "
-                "stall_restarts or a_values");
+                "stall_restarts, a_values or omega");
   int keep = o.keep == 0 ? k : o.keep;
   if (o.keep == RKS_KEEP_AUTO)
     keep = std::max(k, std::min({k + (m - k) / 4, m - 2, rks::kRotMax - 1}));
@@ -1498,14 +1499,11 @@ int rks_create(const rks_csr* A, int32_t k, int32_t m, int32_t d, int32_t which,
   if (!c->ks && o.sketch_kind == RKS_SKETCH_GAUSS) {
     e.gauss_apart = 1;
     const size_t bytes = (size_t)((d + 1) / 2) * n * 16;
-    if (bytes <= rks::kOmegaMax) {
-      if (hipMalloc((void**)&c->om, bytes) == hipSuccess) {
-        rks::launch_omega_fill(e, c->om);
-        e.om = c->om;
-      } else {  // generated by each sketch instead
-        c->om = nullptr;
-        (void)hipGetLastError();
-      }
+    size_t room = 0, total = 0;
+    if (o.omega == RKS_OMEGA_AUTO && bytes <= rks::kOmegaMax && hipMemGetInfo(&room, &total) == hipSuccess &&
+        bytes <= room / rks::kOmegaShare && try_malloc((void**)&c->om, bytes)) {
+      rks::launch_omega_fill(e, c->om);
+      e.om = c->om;
     }
   }
   *out = c;

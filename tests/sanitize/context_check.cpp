@@ -55,6 +55,7 @@ hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::mem
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memmove(d, s, n); return hipSuccess; }
 hipError_t hipMemset(void* d, int v, size_t n) { std::memset(d, v, n); return hipSuccess; }
 hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { std::memset(d, v, n); return hipSuccess; }
+hipError_t hipMemGetInfo(size_t* f, size_t* t) { *f = *t = room; return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipGetLastError() { hipError_t e = last; last = hipSuccess; return e; }
 const char* hipGetErrorString(hipError_t) { return "error"; }
@@ -197,6 +198,24 @@ static void gauss(rks_opts* o) {
   o->graphs = 1;
 }
 
+// Omega is not stored on request, nor where it would take more than 1/32 of the
+// memory that the context's own buffers leave.
+static void omega_left_out() {
+  const size_t om = (size_t)(d + 1) / 2 * n * 16, before = room;
+  rks_ctx* c = context(gauss);
+  const size_t taken = before - room - om;
+  rks_destroy(c);
+  for (int kind = 0; kind < 3; ++kind) {
+    stored = evaluated = 0;
+    room = kind == 0 ? room : taken + 32 * om - (kind == 1 ? 32 : 0);
+    c = kind == 0 ? context([](rks_opts* o) { gauss(o); o->omega = RKS_OMEGA_EVALUATE; }) : context(gauss);
+    CHECK(rks_solve(c, nullptr, 0, nullptr) == RKS_ENOTCONV);
+    CHECK(kind == 2 ? stored > 0 && evaluated == 0 : stored == 0 && evaluated > 0);
+    rks_destroy(c);
+    room = (size_t)1 << 40;
+  }
+}
+
 // A stored Omega gives way to what a context allocates at its first use.
 static void stored_omega() {
   rks_ctx* c = context(gauss);
@@ -225,6 +244,7 @@ static void stored_omega() {
 int main() {
   residual_scratch();
   stored_omega();
+  omega_left_out();
   std::printf("ok: %d failures\n", failures);
   return failures != 0;
 }

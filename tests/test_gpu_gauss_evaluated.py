@@ -1,6 +1,7 @@
 """A Gaussian embedding that a context evaluates instead of storing it (over
-4 GiB), in the extension's own kernel, which sketches w and the pending column
-together: d = 1000, whose 500 pairs leave lanes of the last wave without one.
+4 GiB, or on request), in the extension's own kernel, which sketches w and the
+pending column together: sketch sizes whose pairs leave lanes of the last wave
+without one.
 
 Bars: S = Omega U is a sum of n FP64 products per entry, compared in norm at
 1e-12; a stored column is off by the unit roundoff of its storage, so the
@@ -34,3 +35,38 @@ def test_embedding_over_4_gib(lib, cuda, prec, eps):
         cuda.cuda.synchronize()
         assert np.linalg.norm(z.cpu().numpy() - S[:, t]) < 1e-12, t
     assert np.linalg.norm(S.T @ S - np.eye(m + 1)) < 20 * (m + 1) * eps + 1e-12
+
+
+@pytest.mark.parametrize("N,d", [(37, 62), (91, 131), (181, 300)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32+fx16", "fp32", "bf16"])
+def test_stored_and_evaluated_solves_are_the_same(lib, cuda, prec, N, d):
+    """The decomposition after one extension and the result of restarted solves,
+    bit for bit (recorded graphs included)."""
+    A = convdiff2d(N, (20.0, 10.0))
+    k, m, out = 4, 16, {}
+    for omega in ("auto", "evaluate"):
+        ctx = P.rks_create(A.row_ptr, A.col, A.val, A.n, k, m, d, "LR", 1e-10,
+                           P.rks_opts_default(sketch_kind="gauss", sketch_seed=N, start_seed=1, precision=prec,
+                                              omega=omega, max_restarts=5, graphs=1, refine_tol=1e-2))
+        try:
+            P.rks_arnoldi(ctx)
+            B, S, U = (np.zeros(s, order="F") for s in ((m + 1, m), (d, m + 1), (A.n, m + 1)))
+            P.rks_get_state(ctx, B, S, U)
+            assert np.isfinite(U).all() and (U != 0).any(axis=0).all()
+            P.rks_solve(ctx)
+            ke = P.rks_num_pairs(ctx)
+            re, im, X, res = np.empty(ke), np.empty(ke), np.empty((ke, A.n)), np.empty(ke)
+            P.rks_eigpairs(ctx, re, im, X, res)
+            out[omega] = (B, S, U, re, im, X, res)
+        finally:
+            P.rks_destroy(ctx)
+    for a, b in zip(*out.values()):
+        assert np.array_equal(a, b)
+
+
+def test_unknown_omega_is_refused(lib, cuda):
+    A = convdiff2d(12, (2.0, 1.0))
+    for omega in (-1, 2):
+        with pytest.raises(P.RksError) as ei:
+            P.rks_create(A.row_ptr, A.col, A.val, A.n, 2, 10, 20, "LM", 1e-10, P.rks_opts_default(omega=omega))
+        assert ei.value.code == -1
