@@ -221,7 +221,9 @@ typedef struct {
   /* kernel timings (only when opts.profile > 0), seconds summed over the timed launches */
   double t_spmv, t_reduce, t_ls, t_update, t_rotate;  /* the randomized step runs its least squares
                                                           inside the update launch, so t_update
-                                                          covers both and t_ls stays 0 there */
+                                                          covers both and t_ls stays 0 there; with a
+                                                          Gaussian embedding t_spmv covers the product
+                                                          and the step's pass over Omega */
   int64_t n_spmv, n_update, n_rotate;     /* launches */
   double bytes_spmv, bytes_update, bytes_rotate;  /* algorithmic HBM bytes moved, all launches */
   int64_t n_timed_steps, n_timed_rotate;  /* Arnoldi steps timed per kernel, and rotations */

@@ -2098,33 +2098,34 @@ static void launch_k(const LaunchEnv& e, bool first, bool last, void (*k)(KArgs.
 }
 
 // The Gaussian sketches of x and y (n entries; either may be null) as partial
-// rows of px and py; returns the number of rows (<= kMaxG).
+// rows of px and py; returns the number of rows (<= kMaxG).  Timed with the
+// launcher whose output they sketch: theirs is its last kernel.
 template <typename TX, typename TY, bool HX, bool HY>
-static int gauss_xy_t(const LaunchEnv& e, bool first, const TX* x, const TY* y, double* px, double* py) {
+static int gauss_xy_t(const LaunchEnv& e, const TX* x, const TY* y, double* px, double* py) {
   const int np = (e.sp.d + 1) >> 1;
   int64_t R = (e.n + kMaxG - 1) / kMaxG;
   if (R < kGsMinRows) R = kGsMinRows;
   const int Gx = (int)((e.n + R - 1) / R);
   dim3 grid(Gx, (np + 63) / 64), block(256);
   if (e.om)
-    launch_k(e, first, true, k_gauss_sketch<TX, TY, HX, HY, true>, grid, block, 0, e.n, x, y, R, px, py, e.sp, e.om);
+    launch_k(e, false, true, k_gauss_sketch<TX, TY, HX, HY, true>, grid, block, 0, e.n, x, y, R, px, py, e.sp, e.om);
   else
-    launch_k(e, first, true, k_gauss_sketch<TX, TY, HX, HY, false>, grid, block, 0, e.n, x, y, R, px, py, e.sp,
+    launch_k(e, false, true, k_gauss_sketch<TX, TY, HX, HY, false>, grid, block, 0, e.n, x, y, R, px, py, e.sp,
              nullptr);
   return Gx;
 }
 
 template <typename TX, typename TY>
 static int gauss_xy(const LaunchEnv& e, const TX* x, const TY* y, double* px, double* py) {
-  if (x && y) return gauss_xy_t<TX, TY, true, true>(e, true, x, y, px, py);
-  if (x) return gauss_xy_t<TX, TX, true, false>(e, true, x, nullptr, px, nullptr);
-  return gauss_xy_t<TY, TY, true, false>(e, true, y, nullptr, py, nullptr);
+  if (x && y) return gauss_xy_t<TX, TY, true, true>(e, x, y, px, py);
+  if (x) return gauss_xy_t<TX, TX, true, false>(e, x, nullptr, px, nullptr);
+  return gauss_xy_t<TY, TY, true, false>(e, y, nullptr, py, nullptr);
 }
 
 // The sketch of one vector as the last kernel of a launcher.
 template <typename TX>
 static int gauss_t(const LaunchEnv& e, const TX* x, double* part) {
-  return gauss_xy_t<TX, TX, true, false>(e, false, x, nullptr, part, nullptr);
+  return gauss_xy_t<TX, TX, true, false>(e, x, nullptr, part, nullptr);
 }
 
 // A producer's own Gaussian sketch of what it wrote, unless the caller takes it with launch_gauss.
@@ -2147,7 +2148,7 @@ static int spmv_panel_t(const LaunchEnv& e, const TA* val, const TV* x, TW* w, d
   const size_t bins = bins_lds(e, kSpmvWaves, do_sketch && e.sp_kind == 1);
   const size_t lds = accn * 8 + (stage > bins ? stage : bins);
   RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_spmv_panel<TV, TW, TA, KIND>, lds);
-                    launch_k(e, true, !(do_sketch && gauss_here(e)), k_spmv_panel<TV, TW, TA, KIND>,
+                    launch_k(e, true, !(do_sketch && e.sp_kind == 0), k_spmv_panel<TV, TW, TA, KIND>,
                              dim3(e.npanels), dim3(64 * kSpmvWaves), lds, e.n, e.rows_pp, e.col_pn, val,
                              (const int4*)e.tiles_pn, e.toff_pn, e.off_pn, e.ptile, x, w, zpart, e.sp, do_sketch));
   if (do_sketch && gauss_here(e)) return gauss_t<TW>(e, w, zpart);
@@ -2160,7 +2161,7 @@ static int spmv_sell_t(const LaunchEnv& e, const TS* val, const TV* x, TW* w, do
   if (G >= 8) G &= ~7;  // a multiple of the XCD count (see the slice mapping)
   const size_t lds = bins_lds(e, kSpmvWaves, do_sketch && e.sp_kind == 1);
   RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_spmv_sell<TV, TW, TA, KIND, TS>, lds);
-                    launch_k(e, true, !(do_sketch && gauss_here(e)), k_spmv_sell<TV, TW, TA, KIND, TS>, dim3(G),
+                    launch_k(e, true, !(do_sketch && e.sp_kind == 0), k_spmv_sell<TV, TW, TA, KIND, TS>, dim3(G),
                              dim3(64 * kSpmvWaves), lds, e.rp, e.sl_off, e.nsl, e.col_sl, val, e.vtab, e.n, x, w,
                              zpart, e.sp, do_sketch, e.sl_pad0));
   if (do_sketch && gauss_here(e)) return gauss_t<TW>(e, w, zpart);
@@ -2188,22 +2189,22 @@ int launch_spmv_sketch(const LaunchEnv& e, const void* x, void* w, double* zpart
   const size_t lds = bins_lds(e, kSpmvWaves, do_sketch && e.sp_kind == 1);
   if (prec == 0 && e.vidx) {  // value-indexed FP64 product
     RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_spmv_sketch<double, double, double, KIND, uint8_t>, lds);
-                      launch_k(e, true, !(do_sketch && gauss_here(e)), k_spmv_sketch<double, double, double, KIND, uint8_t>,
+                      launch_k(e, true, !(do_sketch && e.sp_kind == 0), k_spmv_sketch<double, double, double, KIND, uint8_t>,
                                grid, block, lds, e.rp, e.col, e.vidx, e.vtab, (const int4*)e.tiles, e.ntiles,
                                (const double*)x, (double*)w, zpart, e.sp, do_sketch));
   } else if (prec == 0) {
     RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_spmv_sketch<double, double, double, KIND>, lds);
-                      launch_k(e, true, !(do_sketch && gauss_here(e)), k_spmv_sketch<double, double, double, KIND>, grid, block, lds,
+                      launch_k(e, true, !(do_sketch && e.sp_kind == 0), k_spmv_sketch<double, double, double, KIND>, grid, block, lds,
                                e.rp, e.col, e.val, nullptr, (const int4*)e.tiles, e.ntiles, (const double*)x, (double*)w,
                                zpart, e.sp, do_sketch));
   } else if (prec == 1) {
     RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_spmv_sketch<float, float, float, KIND>, lds);
-                      launch_k(e, true, !(do_sketch && gauss_here(e)), k_spmv_sketch<float, float, float, KIND>, grid, block, lds,
+                      launch_k(e, true, !(do_sketch && e.sp_kind == 0), k_spmv_sketch<float, float, float, KIND>, grid, block, lds,
                                e.rp, e.col, e.val32, nullptr, (const int4*)e.tiles, e.ntiles, (const float*)x, (float*)w,
                                zpart, e.sp, do_sketch));
   } else {
     RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_spmv_sketch<bf16_t, float, float, KIND>, lds);
-                      launch_k(e, true, !(do_sketch && gauss_here(e)), k_spmv_sketch<bf16_t, float, float, KIND>, grid, block, lds,
+                      launch_k(e, true, !(do_sketch && e.sp_kind == 0), k_spmv_sketch<bf16_t, float, float, KIND>, grid, block, lds,
                                e.rp, e.col, e.val32, nullptr, (const int4*)e.tiles, e.ntiles, (const bf16_t*)x, (float*)w,
                                zpart, e.sp, do_sketch));
   }

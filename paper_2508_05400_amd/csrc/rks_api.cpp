@@ -289,10 +289,11 @@ int arnoldi_step(rks_ctx* c, int t) {
   {
     ProfK p(c, CAT_SPMV, timed, e);
     c->G_z = rks::launch_spmv_sketch(p.env, spmv_x(c, t), c->w, c->zpart, 1, spmv_prec(c));
+    // a Gaussian Omega: of w and of the pending column in one pass over its
+    // entries, timed with the product
+    if (e.sp_kind == 0)
+      c->G_z = c->G_s = rks::launch_gauss(p.env, c->w, c->pending ? basis_col(c, t) : nullptr, c->zpart, c->spart);
   }
-  // a Gaussian Omega: of w and of the pending column in one pass over its entries
-  if (e.sp_kind == 0)
-    c->G_z = c->G_s = rks::launch_gauss(e, c->w, c->pending ? basis_col(c, t) : nullptr, c->zpart, c->spart);
   {
     ProfK p(c, CAT_REDUCE, timed, e);
     rks::launch_reduce(p.env, c->zpart, c->G_z, c->pending ? c->spart : nullptr, c->G_s, c->z, c->sr);
