@@ -1038,9 +1038,19 @@ __device__ __forceinline__ double pair_unit(float hi, int s) {
   return __longlong_as_double((long long)((unsigned long long)(k + 1023) << 52));
 }
 __device__ __forceinline__ double pair_val(float hi, int16_t lo) { return (double)hi + (double)lo * pair_unit(hi, 1); }
+// x is the FP64 number passed in: where it is a product, the compiler must not
+// contract x - hi with it, which would split the product before its rounding.
 __device__ __forceinline__ void split_pair(double x, float& hi, int16_t& lo) {
+#pragma clang fp contract(off)
   hi = (float)x;
   lo = (int16_t)__builtin_rint((x - (double)hi) * pair_unit(hi, -1));
+}
+// The pair of the product a b before its rounding to FP64 (hi from the rounded
+// product, the remainder from a fused multiply-add).
+__device__ __forceinline__ void split_pair_product(double a, double b, float& hi, int16_t& lo) {
+#pragma clang fp contract(off)
+  hi = (float)(a * b);
+  lo = (int16_t)__builtin_rint(__builtin_fma(a, b, -(double)hi) * pair_unit(hi, -1));
 }
 
 // One packet of a basis column: PB bytes of TV values and, for the pair basis
@@ -1456,9 +1466,6 @@ __global__ __launch_bounds__(512) void k_init(int64_t n, TV* __restrict__ u, con
     for (; i < n; i += stride) {
       double v, g1;
       gauss_pair((uint64_t)i, c2, tag, s0, s1, v, g1);
-      // rounded to FP64 here: otherwise the pair's remainder x - hi is contracted
-      // with the product that v is, and splits the unrounded vector
-      asm("" : "+v"(v));
       row(i, v);
     }
   } else {
@@ -1649,7 +1656,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(YG || (SPLI
         if constexpr (SPLIT) {
           float hi;
           int16_t lo;
-          split_pair(pair_val(xe.v[r], xel.v[r]) * xscale, hi, lo);
+          split_pair_product(pair_val(xe.v[r], xel.v[r]), xscale, hi, lo);
           xd[r] = hi;
           ((int16_t*)Ulo)[row + r + (int64_t)xdst * ldu] = lo;
           xcur[row + r] = pair_val(hi, lo);
