@@ -1094,8 +1094,8 @@ struct ColPk {
 // (the next product with A reads it there).
 // Each thread owns V consecutive rows and streams every basis column once
 // with one 16-byte load per column (plain for the first nkeep columns, non-
-// temporal for the others, see kept_columns), in groups of 8 (8 loads, then
-// their FMAs).  ROLL: a rolling window of 8 instead, where the slot of
+// temporal for the others, see kept_columns; the up to 7 columns left over by
+// the groups are always plain), in groups of 8 (8 loads, then their FMAs).  ROLL: a rolling window of 8 instead, where the slot of
 // column l is refilled with column l + 8 as soon as it is consumed.  Measured:
 // the window pays in k_ls_update without its prefetch when each thread walks
 // 4 or more packets (one 16-wave workgroup per CU; 393 -> 364 us per launch
@@ -2244,8 +2244,10 @@ void launch_ls(const LaunchEnv& e, int t, int pending, int finalize_only, const 
 
 // Leading basis columns that a pass over ncol of them reads with plain loads,
 // so that they stay in the 256 MB Infinity Cache until the next step's pass (a
-// multiple of 8, the groups of the column walk); the others are read non-
-// temporally and leave the cache alone.  Reading every column non-temporally
+// multiple of 8, the groups of the column walk); the other groups are read non-
+// temporally and leave the cache alone (the fewer than 8 columns after the last
+// group of the update, and the leading ones that k_ls_update prefetches, are
+// plain whatever this rule says).  ncol counts the column that the step writes.  Reading every column non-temporally
 // puts the whole pass on HBM; reading more of them plainly than fit evicts
 // each before it is read again (least recently used over a cyclic walk), and
 // A, x and w want a share too.  All are kept up to 320 MB (a step's later
@@ -2275,7 +2277,7 @@ int launch_update(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, cons
   const size_t lds = ((size_t)kMaxM + 2) * 8 + bins_lds(e, 16, true);
   k_update<double, double, 2><<<G, 1024, lds, e.stream>>>(e.n, npk, ncol, (const double*)U, ldu, (const double*)w, cs,
                                                          yraw, scale, h, accumulate, (double*)unew, spart, e.sp,
-                                                         kept_columns(e, ncol));
+                                                         kept_columns(e, ncol + 1));
   return G;
 }
 
@@ -2506,7 +2508,7 @@ int launch_dots(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, const 
   const int V = 16 / e.vbytes();
   const int64_t npk = (e.n + V - 1) / V;
   const int G = grid_for(npk, 1024, kMaxG);
-  const int nkeep = kept_columns(e, ncol);
+  const int nkeep = kept_columns(e, ncol + 1);  // (as the update of the same step)
   if (e.prec == 0) {
     k_dots<double, double><<<G, 1024, 0, e.stream>>>(e.n, npk, ncol, (const double*)U, ldu, (const double*)x, part, nkeep);
   } else if (e.prec == 1) {
