@@ -62,13 +62,18 @@ def target_basis(X: np.ndarray, N: int) -> np.ndarray:
 
 
 def _one_range(tensors, like) -> bool:
-    """Whether the tensors follow one another in memory, with the sizes of those of like."""
-    at = tensors[0].data_ptr()
+    """Whether tensors are tensors that follow one another in memory, with the sizes of those of like."""
+    import torch
+    if not like or len(tensors) != len(like):
+        return False
+    at = None
     for t, p in zip(tensors, like):
-        if t.data_ptr() != at or t.numel() != p.numel() or t.element_size() != 4 or not t.is_contiguous():
+        if not isinstance(t, torch.Tensor) or t.element_size() != 4 or t.numel() != p.numel() or not t.is_contiguous():
             return False
-        at += 4 * t.numel()
-    return len(tensors) == len(like)
+        if at is not None and t.data_ptr() != at:
+            return False
+        at = t.data_ptr() + 4 * t.numel()
+    return True
 
 
 class StartNet:
