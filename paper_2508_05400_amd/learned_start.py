@@ -83,7 +83,7 @@ class StartNet:
         import torch
         self.torch = torch
         rng = np.random.default_rng(seed)
-        self.w, self.b = self._views(torch.zeros(PARAMS, dtype=torch.float32, device="cuda"))
+        self.w, self.b = self._parameters(torch.zeros(PARAMS, dtype=torch.float32, device="cuda"))
         for w, (cin, cout, _) in zip(self.w, LAYERS):
             std = np.sqrt(2.0 / (cin * 9))
             w.copy_(torch.tensor(rng.standard_normal((cout, cin, 3, 3)) * std, dtype=torch.float32))
@@ -97,6 +97,12 @@ class StartNet:
         (so that one Adam launch covers them; twelve took 54 of a 670 us step)."""
         parts = flat.split([o * c * 9 for c, o, _ in LAYERS] + [o for _, o, _ in LAYERS])
         return [p.view(o, c, 3, 3) for p, (c, o, _) in zip(parts, LAYERS)], list(parts[len(LAYERS):])
+
+    @classmethod
+    def _parameters(cls, flat):
+        """The same as tensors that are no views: those share a version, and a write
+        to one parameter would invalidate what autograd saved of another."""
+        return tuple([p.data for p in q] for q in cls._views(flat))
 
     def forward(self, x):
         """x: (Bn, 2, 64, 64) float32 device tensor -> list of activations."""

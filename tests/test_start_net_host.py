@@ -9,7 +9,7 @@ def _net(monkeypatch):
     """A network with its parameters in host memory, and the Adam calls it makes."""
     net, calls = L.StartNet.__new__(L.StartNet), []
     net.torch, net.t = torch, 0
-    net.w, net.b = L.StartNet._views(torch.zeros(L.PARAMS))
+    net.w, net.b = L.StartNet._parameters(torch.zeros(L.PARAMS))
     net.m, net.v = (sum(L.StartNet._views(torch.zeros(L.PARAMS)), []) for _ in range(2))
     monkeypatch.setattr(L.B, "rks_net_adam", lambda *a: calls.append(a))
     return net, calls
@@ -30,3 +30,15 @@ def test_adam_takes_device_addresses_and_short_lists(monkeypatch):
     assert not calls and net.t == 3
     net.adam(gw, gb, 1e-3)
     assert [c[4] for c in calls] == [L.PARAMS]
+
+
+def test_parameters_are_tensors_of_their_own(monkeypatch):
+    """Writing to one parameter does not invalidate what autograd saved of another."""
+    net, _ = _net(monkeypatch)
+    assert not any(t._is_view() for t in net.w + net.b)
+    net.w[0].requires_grad_()
+    loss = (net.w[0] * net.w[0]).sum()
+    net.w[1].mul_(0.5)
+    net.b[0].add_(1.0)
+    loss.backward()
+    assert net.b[1].abs().max() == 0 and net.b[0].min() == 1  # of one buffer, without overlap
