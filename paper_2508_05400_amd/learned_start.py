@@ -173,8 +173,8 @@ class StartNet:
         net = cls(seed=0)
         with np.load(path, allow_pickle=False) as z:
             for i in range(len(LAYERS)):
-                net.w[i].copy_(torch.tensor(z[f"w{i}"], dtype=torch.float32))
-                net.b[i].copy_(torch.tensor(z[f"b{i}"], dtype=torch.float32))
+                for p, a in ((net.w[i], z[f"w{i}"]), (net.b[i], z[f"b{i}"])):
+                    p.copy_(torch.tensor(a, dtype=torch.float32).reshape(p.shape))
         return net
 
 

@@ -1,5 +1,6 @@
 """Host side of the start network's parameter handling (no device needed)."""
 import numpy as np
+import pytest
 import torch
 
 from paper_2508_05400_amd import learned_start as L
@@ -42,3 +43,21 @@ def test_parameters_are_tensors_of_their_own(monkeypatch):
     net.b[0].add_(1.0)
     loss.backward()
     assert net.b[1].abs().max() == 0 and net.b[0].min() == 1  # of one buffer, without overlap
+
+
+def test_load_takes_any_shape_of_the_right_size(monkeypatch, tmp_path):
+    """Saved arrays replace the parameters entry by entry, in whatever shape they
+    are; another number of entries is refused rather than broadcast."""
+    net, _ = _net(monkeypatch)
+    monkeypatch.setattr(L.StartNet, "__init__", lambda self, seed=0: self.__dict__.update(net.__dict__))
+    rng = np.random.default_rng(1)
+    arrs = {f"w{i}": rng.standard_normal((o, c * 9)).astype(np.float32) for i, (c, o, _) in enumerate(L.LAYERS)}
+    arrs.update({f"b{i}": rng.standard_normal((o, 1)).astype(np.float32) for i, (_, o, _) in enumerate(L.LAYERS)})
+    np.savez(tmp_path / "a.npz", **arrs)
+    got = L.StartNet.load(str(tmp_path / "a.npz"))
+    for i in range(len(L.LAYERS)):
+        assert np.array_equal(got.w[i].numpy().ravel(), arrs[f"w{i}"].ravel())
+        assert np.array_equal(got.b[i].numpy().ravel(), arrs[f"b{i}"].ravel())
+    np.savez(tmp_path / "b.npz", **dict(arrs, b0=np.float32(1.0)))
+    with pytest.raises(RuntimeError):
+        L.StartNet.load(str(tmp_path / "b.npz"))
