@@ -20,18 +20,6 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// Sum over the block; every thread gets the total.  red holds >= 16 doubles.
-__device__ __forceinline__ double block_sum(double v, double* red) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-  v = wave_sum(v);
-  __syncthreads();
-  if (lane == 0) red[wv] = v;
-  __syncthreads();
-  double t = 0.0;
-  for (int q = 0; q < nw; ++q) t += red[q];
-  return t;
-}
-
 // Scatter v * Omega[:, i] into the block's LDS bins (unscaled).
 // KIND 1: sparse-sign Omega, accumulated by the producing kernel; 2: no
 // sketch (deterministic Krylov-Schur, whose kernels accumulate a squared norm
@@ -1088,7 +1076,7 @@ struct ColPk {
 };
 
 // u~ = coef[ncol] * w - sum_{l < ncol} coef[l] U(:, l), stored (rounded to the
-// basis precision) as the new column; partials of Omega of the stored value.
+// basis precision) as the new column; partials of a sparse Omega of the stored value.
 // SPLIT: the basis is the pair basis (U, Ulo; the new column to unew,
 // unew_lo), and the stored value of the new column also goes to xout in FP64
 // (the next product with A reads it there).
@@ -1233,14 +1221,13 @@ __device__ __forceinline__ void update_body(int64_t n, int64_t npk, int ncol, co
 // y_l = cs_l yraw_l sc, coef_l = cs_l y_l, coef_ncol = sc.  Workgroup 0 stores
 // h = y (first pass) or h += y.  (As launches of their own, one workgroup
 // each, the coefficients took 4.4 us per pass.)
-template <typename TV, typename TW, int KIND>
-__global__ __launch_bounds__(1024) void k_update(int64_t n, int64_t npk, int ncol, const TV* __restrict__ U,
-                                                int64_t ldu, const TW* __restrict__ w,
+__global__ __launch_bounds__(1024) void k_update(int64_t n, int64_t npk, int ncol, const double* __restrict__ U,
+                                                int64_t ldu, const double* __restrict__ w,
                                                 const double* __restrict__ cs, const double* __restrict__ yraw,
                                                 const double* __restrict__ scale, double* __restrict__ h,
-                                                int accumulate, TV* __restrict__ unew, double* __restrict__ spart,
-                                                SketchP sp, int nkeep) {
-  extern __shared__ double smem[];  // the coefficients (kMaxM + 2), then 16 waves x d (none for KIND 3)
+                                                int accumulate, double* __restrict__ unew,
+                                                double* __restrict__ spart, SketchP sp, int nkeep) {
+  extern __shared__ double smem[];  // the coefficients (kMaxM + 2), then one value per wave
   double* coef = smem;
   const double sc = scale ? *scale : 1.0;
   for (int l = threadIdx.x; l < ncol; l += blockDim.x) {
@@ -1250,8 +1237,8 @@ __global__ __launch_bounds__(1024) void k_update(int64_t n, int64_t npk, int nco
   }
   if (threadIdx.x == 0) coef[ncol] = sc;
   __syncthreads();
-  update_body<TV, TW, KIND>(n, npk, ncol, U, ldu, w, coef, unew, spart, sp, smem + kMaxM + 2, nullptr, false, nullptr,
-                            nullptr, nullptr, nkeep);
+  update_body<double, double, 2>(n, npk, ncol, U, ldu, w, coef, unew, spart, sp, smem + kMaxM + 2, nullptr, false,
+                                 nullptr, nullptr, nullptr, nkeep);
 }
 
 // One randomized Arnoldi step's least squares and update in one launch: every
@@ -1334,11 +1321,10 @@ __device__ __forceinline__ double wave_sum8(const double v[8], int lane) {
 // for the Euclidean Gram-Schmidt of deterministic Krylov-Schur.  Each thread
 // owns one 16-byte packet of rows (as in k_update); columns go in groups of
 // eight with one wave_sum8 per group.
-template <typename TV, typename TX>
-__global__ __launch_bounds__(1024) void k_dots(int64_t n, int64_t npk, int ncol, const TV* __restrict__ U,
-                                               int64_t ldu, const TX* __restrict__ x, double* __restrict__ part,
+__global__ __launch_bounds__(1024) void k_dots(int64_t n, int64_t npk, int ncol, const double* __restrict__ U,
+                                               int64_t ldu, const double* __restrict__ x, double* __restrict__ part,
                                                int nkeep) {
-  constexpr int V = 16 / sizeof(TV);
+  constexpr int V = 2;
   __shared__ double bins[16][kMaxM + 8];  // one row per wave, added in wave order at the end
   for (int b = threadIdx.x; b < 16 * (kMaxM + 8); b += blockDim.x) bins[b / (kMaxM + 8)][b % (kMaxM + 8)] = 0.0;
   __syncthreads();
@@ -1350,8 +1336,8 @@ __global__ __launch_bounds__(1024) void k_dots(int64_t n, int64_t npk, int ncol,
     const int64_t i0 = g * V;
     double xv[V];
 #pragma unroll
-    for (int r = 0; r < V; ++r) xv[r] = (act && i0 + r < n) ? Conv<TX>::ld(x[i0 + r]) : 0.0;
-    const TV* col0 = U + i0;
+    for (int r = 0; r < V; ++r) xv[r] = (act && i0 + r < n) ? x[i0 + r] : 0.0;
+    const double* col0 = U + i0;
     auto walk = [&](auto keep, int l0, int l1) {  // columns l0 .. l1 - 1 (see kept_columns)
       for (; l0 < l1; l0 += 8) {
         double v[8];
@@ -1359,12 +1345,12 @@ __global__ __launch_bounds__(1024) void k_dots(int64_t n, int64_t npk, int ncol,
         for (int q = 0; q < 8; ++q) {
           v[q] = 0.0;
           if (act && l0 + q < ncol) {
-            Pack16<TV> p;
+            Pack16<double> p;
             const u32x4* src = (const u32x4*)(col0 + (int64_t)(l0 + q) * ldu);
             if constexpr (decltype(keep)::value) p.raw = *src;
             else p.raw = __builtin_nontemporal_load(src);
 #pragma unroll
-            for (int r = 0; r < V; ++r) v[q] += Conv<TV>::ld(p.v[r]) * xv[r];
+            for (int r = 0; r < V; ++r) v[q] += p.v[r] * xv[r];
           }
         }
         const double sv = wave_sum8(v, lane);
@@ -1423,7 +1409,8 @@ __global__ __launch_bounds__(1024) void k_ks_finalize(int t, const double* __res
 
 // First column: u0 (device FP64) or a seeded N(0,1) vector (Philox counter
 // (i, c2, tag): tag 2 the start vector, tag 3 the replacement after a
-// breakdown), stored in TV when `store`; partials of Omega of the stored value.
+// breakdown), stored in TV when `store`; partials of a sparse Omega of the
+// stored value.
 // SPLIT (TV = float): stored as the pair (u, ulo; see split_pair), the stored
 // value also to xout in FP64.
 // GEN: the vector is generated; otherwise it is u0, whose values are loaded
@@ -1910,11 +1897,6 @@ __global__ __launch_bounds__(256) void k_normalise(int64_t n, double* __restrict
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) x[i] *= sc;
 }
 
-__global__ __launch_bounds__(256) void k_fill(int64_t n, double* __restrict__ x, double v) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) x[i] = v;
-}
-
 // Plain streaming copy of n 16-byte packets (bandwidth reference).
 __global__ __launch_bounds__(256) void k_copy16(const u32x4* __restrict__ src, u32x4* __restrict__ dst, int64_t n) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -2135,7 +2117,7 @@ static int gauss_t(const LaunchEnv& e, const TX* x, double* part) {
   return gauss_xy_t<TX, TX, true, false>(e, x, nullptr, part, nullptr);
 }
 
-// A producer's own Gaussian sketch of what it wrote, unless the caller takes it with launch_gauss.
+// The SpMV's own Gaussian sketch of what it wrote, unless the caller takes it with launch_gauss.
 static bool gauss_here(const LaunchEnv& e) { return e.sp_kind == 0 && !e.gauss_apart; }
 
 int launch_gauss(const LaunchEnv& e, const void* w, const void* u, double* pw, double* pu) {
@@ -2275,9 +2257,8 @@ int launch_update(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, cons
   const int64_t npk = (e.n + 1) / 2;
   const int G = grid_for(npk, 1024, kMaxG);
   const size_t lds = ((size_t)kMaxM + 2) * 8 + bins_lds(e, 16, true);
-  k_update<double, double, 2><<<G, 1024, lds, e.stream>>>(e.n, npk, ncol, (const double*)U, ldu, (const double*)w, cs,
-                                                         yraw, scale, h, accumulate, (double*)unew, spart, e.sp,
-                                                         kept_columns(e, ncol + 1));
+  k_update<<<G, 1024, lds, e.stream>>>(e.n, npk, ncol, (const double*)U, ldu, (const double*)w, cs, yraw, scale, h,
+                                       accumulate, (double*)unew, spart, e.sp, kept_columns(e, ncol + 1));
   return G;
 }
 
@@ -2289,10 +2270,10 @@ static void ls_update_t(const LaunchEnv& e, dim3 grid, size_t lds, int t, int pe
   const int16_t* Ulo = SPLIT ? e.lo_of(U) : nullptr;
   int16_t* unew_lo = SPLIT ? e.lo_of(unew) : nullptr;
   double* xout = SPLIT ? e.xcur : nullptr;
-  RKS_SKETCH_SWITCH(e.sp_kind, lds_allow((const void*)k_ls_update<TV, TW, KIND, PRE, PB, ROLL, SPLIT>, lds);
-                    launch_k(e, true, !gauss_here(e), k_ls_update<TV, TW, KIND, PRE, PB, ROLL, SPLIT>, grid, dim3(1024),
-                             lds, t, e.sp.d, pending, zraw, sraw, S, B, ldb, E, cs, coef, scal, flags, bd_rel, e.n,
-                             npk, (const TV*)U, ldu, (const TW*)w, (TV*)unew, spart, e.sp, Ulo, unew_lo, xout, nkeep));
+  auto k = e.sp_kind == 1 ? k_ls_update<TV, TW, 1, PRE, PB, ROLL, SPLIT> : k_ls_update<TV, TW, 3, PRE, PB, ROLL, SPLIT>;
+  lds_allow((const void*)k, lds);
+  launch_k(e, true, true, k, grid, dim3(1024), lds, t, e.sp.d, pending, zraw, sraw, S, B, ldb, E, cs, coef, scal, flags,
+           bd_rel, e.n, npk, (const TV*)U, ldu, (const TW*)w, (TV*)unew, spart, e.sp, Ulo, unew_lo, xout, nkeep);
 }
 
 int launch_ls_update(const LaunchEnv& e, int t, int pending, const double* zraw, const double* sraw, double* S,
@@ -2337,12 +2318,6 @@ int launch_ls_update(const LaunchEnv& e, int t, int pending, const double* zraw,
 #undef RKS_LSU
 #undef RKS_LSU_PB
 #undef RKS_LSU_T
-  if (gauss_here(e)) {  // sketch of the stored value (the pair basis: of its FP64 copy)
-    if (e.prec == 0) return gauss_t<double>(e, (const double*)unew, spart);
-    if (e.prec == 1) return gauss_t<float>(e, (const float*)unew, spart);
-    if (e.prec == 2) return gauss_t<bf16_t>(e, (const bf16_t*)unew, spart);
-    return gauss_t<double>(e, e.xcur, spart);
-  }
   return G;
 }
 
@@ -2373,14 +2348,8 @@ int launch_init(const LaunchEnv& e, void* u, const double* u0, uint32_t s0, uint
     init_t<bf16_t, false>(e, G, (bf16_t*)u, u0, s0, s1, c2, tag, spart, store, nullptr, nullptr);
   else
     init_t<float, true>(e, G, (float*)u, u0, s0, s1, c2, tag, spart, store, store ? e.lo_of(u) : nullptr, e.xcur);
-  if (e.sp_kind == 0 && !(store && e.gauss_apart)) {
-    // sketch of the stored value; without a store, of u0 itself (FP64 only)
-    if (!store) return u0 ? gauss_t<double>(e, u0, spart) : 0;
-    if (prec == 0) return gauss_t<double>(e, (const double*)u, spart);
-    if (prec == 1) return gauss_t<float>(e, (const float*)u, spart);
-    if (prec == 2) return gauss_t<bf16_t>(e, (const bf16_t*)u, spart);
-    return gauss_t<double>(e, e.xcur, spart);
-  }
+  // a Gaussian Omega: of u0 itself (FP64) without a store; launch_gauss takes that of a stored value
+  if (e.sp_kind == 0 && !store) return u0 ? gauss_t<double>(e, u0, spart) : 0;
   return G;
 }
 
@@ -2504,20 +2473,12 @@ void launch_normalise(const LaunchEnv& e, double* X, int ke, const int* kind, co
   k_normalise<<<dim3(grid_for(e.n, 1024, 256), ke), 256, 0, e.stream>>>(e.n, X, sums, k);
 }
 
-int launch_dots(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, const void* x, int x_is_basis, double* part) {
-  const int V = 16 / e.vbytes();
-  const int64_t npk = (e.n + V - 1) / V;
+int launch_dots(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, const void* x, double* part) {
+  const int64_t npk = (e.n + 1) / 2;
   const int G = grid_for(npk, 1024, kMaxG);
-  const int nkeep = kept_columns(e, ncol + 1);  // (as the update of the same step)
-  if (e.prec == 0) {
-    k_dots<double, double><<<G, 1024, 0, e.stream>>>(e.n, npk, ncol, (const double*)U, ldu, (const double*)x, part, nkeep);
-  } else if (e.prec == 1) {
-    k_dots<float, float><<<G, 1024, 0, e.stream>>>(e.n, npk, ncol, (const float*)U, ldu, (const float*)x, part, nkeep);
-  } else if (x_is_basis) {
-    k_dots<bf16_t, bf16_t><<<G, 1024, 0, e.stream>>>(e.n, npk, ncol, (const bf16_t*)U, ldu, (const bf16_t*)x, part, nkeep);
-  } else {
-    k_dots<bf16_t, float><<<G, 1024, 0, e.stream>>>(e.n, npk, ncol, (const bf16_t*)U, ldu, (const float*)x, part, nkeep);
-  }
+  // (kept as in the update of the same step)
+  k_dots<<<G, 1024, 0, e.stream>>>(e.n, npk, ncol, (const double*)U, ldu, (const double*)x, part,
+                                   kept_columns(e, ncol + 1));
   return G;
 }
 
@@ -2584,10 +2545,6 @@ void launch_read16(hipStream_t stream, const void* src, int64_t packets) {
 
 void launch_copy16(hipStream_t stream, const void* src, void* dst, int64_t packets) {
   k_copy16<<<grid_for(packets, 256, 8192), 256, 0, stream>>>((const u32x4*)src, (u32x4*)dst, packets);
-}
-
-void launch_fill(const LaunchEnv& e, int64_t len, double* x, double v) {
-  k_fill<<<grid_for(len, 256, kMaxG), 256, 0, e.stream>>>(len, x, v);
 }
 
 }  // namespace rks

@@ -28,9 +28,9 @@ struct LaunchEnv {
   int sp_kind;         // 0 Gaussian (applied by k_gauss_sketch), 1 sparse-sign, 2 none (deterministic KS)
   SketchP sp;
   // Gaussian Omega (sp_kind 0) of a context: its unscaled entries, column
-  // after column, d rounded up to even of each, or null to generate them; gauss_apart:
-  // the producers do not sketch what they write, launch_gauss does it for two
-  // of them together
+  // after column, d rounded up to even of each, or null to generate them.  The
+  // update and the start vector leave its sketch to launch_gauss, and with
+  // gauss_apart the SpMV does, too: launch_gauss takes two vectors together
   const double* om = nullptr;
   int gauss_apart = 0;
   // column-blocked SpMV (used when cb = 1): the layout of panels.hpp, one
@@ -96,14 +96,15 @@ void launch_ls(const LaunchEnv& e, int t, int pending, int finalize_only, const 
 int launch_update(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, const void* w, const double* cs,
                   const double* yraw, const double* scale, double* h, int accumulate, void* unew, double* spart);
 // Least squares (as launch_ls, not finalize-only) and update (unew = w - U h over
-// the t + 1 columns, partials of its sketch) in one launch; returns the number of partial rows.
+// the t + 1 columns, partials of its sparse sketch) in one launch; returns the number of partial rows.
 int launch_ls_update(const LaunchEnv& e, int t, int pending, const double* zraw, const double* sraw, double* S,
                      double* B, int ldb, double* E, double* cs, double* coef, double* scal, int* flags,
                      double bd_rel, const void* U, int64_t ldu, const void* w, void* unew, double* spart);
 // u = u0, or the seeded N(0,1) vector of Philox counter (i, c2, tag) (tag 2:
 // start vector, tag 3: breakdown replacement), stored in the basis type (or
-// prec_override's); partials of Omega of the stored value.  The pair basis
-// (prec 3) also writes the stored value to xcur.
+// prec_override's); partials of a sparse Omega of the stored value.  Without
+// store, of any Omega of u0 (FP64).  The pair basis (prec 3) also writes the
+// stored value to xcur.
 int launch_init(const LaunchEnv& e, void* u, const double* u0, uint32_t s0, uint32_t s1, double* spart, int store,
                 int prec_override, uint32_t c2 = 0, uint32_t tag = 2);
 // O(:, out0 .. out0 + kout) = U(:, in0 .. in0 + min) Y.  ldu must be a multiple of
@@ -121,13 +122,12 @@ int launch_resid(const LaunchEnv& e, int64_t nnz, const double* X, int ke, const
                  const double* im, double* Xi, int xcols, double* part);
 // Scales every pair of X to unit norm, sums being the sums of launch_resid's rows.
 void launch_normalise(const LaunchEnv& e, double* X, int ke, const int* kind, const double* sums);
-void launch_fill(const LaunchEnv& e, int64_t len, double* x, double v);
 void launch_copy16(hipStream_t stream, const void* src, void* dst, int64_t packets);
 void launch_read16(hipStream_t stream, const void* src, int64_t packets);
 // Deterministic Krylov-Schur (Euclidean classical Gram-Schmidt, twice):
 // partials of U(:, 0:ncol)^T x (returns the number of partial rows), their sum,
 // and the closing of a step from the G partials of its last pass.
-int launch_dots(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, const void* x, int x_is_basis, double* part);
+int launch_dots(const LaunchEnv& e, int ncol, const void* U, int64_t ldu, const void* x, double* part);
 void launch_reduce_len(const LaunchEnv& e, const double* pa, int Ga, double* oa, int len);
 void launch_ks_finalize(const LaunchEnv& e, int t, const double* h, const double* part, int G, double* B, int ldb,
                         double* cs, int* flags, double bd_rel);

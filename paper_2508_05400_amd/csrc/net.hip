@@ -69,8 +69,8 @@ struct Plane<uint32_t> {
 // A lane owns one pixel and OT output channels, so an input value is loaded
 // once per tap for OT products, and the weights, which all lanes share, come
 // through scalar loads; the nine taps of CU input channels are loaded before
-// their first product (from addresses clamped into the image), contiguous
-// across a wave.
+// their first product (0 from offsets out of range for taps outside the
+// image), contiguous across a wave.
 template <int OT, int CU, bool BWD, bool RELU, typename IT>
 __global__ __launch_bounds__(256) void k_conv(const float* __restrict__ in, const float* __restrict__ act,
                                               const float* __restrict__ w, const float* __restrict__ bias,
@@ -144,13 +144,8 @@ __global__ __launch_bounds__(256) void k_conv(const float* __restrict__ in, cons
   }
 }
 
-// dw[o, c, tap] = sum_{b, pixel} g[b, o, pixel] x[b, c, pixel + offset(tap)];
-// db[o] = sum g[b, o, :] (g = dy, masked by y > 0 when RELU).  Every sum is
-// 256 chains of fused multiply-adds (chain t takes the pixels t, t + 256, ...
-// of the whole batch in order, leaving out g = 0 and taps outside the image),
-// added by a fixed tree, so it does not depend on how the work is split.
-// One chain of dw with g = 0 and outside taps left out one by one: for sums
-// that came out infinite or NaN (see k_conv_bwd_filter).
+// One chain of k_conv_bwd_filter with g = 0 and outside taps left out one by
+// one: for sums that came out infinite or NaN.
 template <bool RELU>
 __device__ __attribute__((noinline)) float filter_masked(const float* __restrict__ x, const float* __restrict__ dy,
                                                          const float* __restrict__ y, int B, int C, int O, int H,
@@ -171,13 +166,18 @@ __device__ __attribute__((noinline)) float filter_masked(const float* __restrict
   return acc;
 }
 
-// A workgroup owns OT output channels, one input channel and NT taps (9, or
+// dw[o, c, tap] = sum_{b, pixel} g[b, o, pixel] x[b, c, pixel + offset(tap)];
+// db[o] = sum g[b, o, :] (g = dy, masked by y > 0 when RELU).  Every sum is
+// 256 chains of fused multiply-adds (chain t takes the pixels t, t + 256, ...
+// of the whole batch in order, leaving out g = 0 and taps outside the image),
+// added by a fixed tree, so it does not depend on how the work is split.
+// A workgroup owns one output channel, one input channel and NT taps (9, or
 // the 3 of one row of the filter); its thread t runs chain t of all of them,
 // with the loads of U pixels issued before the first product.  Taps outside
-// the image read a clamped address and count as x = 0.  g = 0 and x = 0 leave
-// a finite sum as it is; a chain that ends infinite or NaN is run again with
-// them left out.
-template <int OT, int NT, int U, bool RELU, typename IT, bool TINY>
+// the image have an offset out of range, which reads x = 0.  g = 0 and x = 0
+// leave a finite sum as it is; a chain that ends infinite or NaN is run again
+// with them left out.
+template <int NT, int U, bool RELU, typename IT, bool TINY>
 __global__ __launch_bounds__(256) void k_conv_bwd_filter(const float* __restrict__ x, const float* __restrict__ dy,
                                                          const float* __restrict__ y, float* __restrict__ dw,
                                                          float* __restrict__ db, int B, int C, int O, int H, int W,
@@ -185,15 +185,11 @@ __global__ __launch_bounds__(256) void k_conv_bwd_filter(const float* __restrict
   constexpr int NR3 = NT / 3;
   const int HW = H * W;
   const int tg = blockIdx.x % (9 / NT), oc = blockIdx.x / (9 / NT);
-  const int c = oc % C, o0 = oc / C * OT, t0 = tg * NT;
+  const int c = oc % C, o = oc / C, t0 = tg * NT;
   const int64_t npix = (int64_t)B * HW;
-  float acc[OT][NT], ab[OT];
+  float acc[NT], ab = 0.f;
 #pragma unroll
-  for (int k = 0; k < OT; ++k) {
-    ab[k] = 0.f;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[k][t] = 0.f;
-  }
+  for (int t = 0; t < NT; ++t) acc[t] = 0.f;
   // the chain's pixel: column j, row offset rw = W i, and the byte offsets
   // xo, go of its sample in x and dy; one step is 256 pixels
   const int sj = 256 % W, srw = 256 / W * W;
@@ -204,17 +200,14 @@ __global__ __launch_bounds__(256) void k_conv_bwd_filter(const float* __restrict
   IT xo = (IT)((int)threadIdx.x / HW) * xs, go = (IT)((int)threadIdx.x / HW) * gs;
   const float* xc = x + (int64_t)c * HW;
   const Plane<IT> px(xc, npix * C - (int64_t)c * HW);
-  auto load = [&](int64_t q, float(&g)[U][OT], float(&yv)[U][OT], float(&v)[U][NT]) {
+  const int64_t ch = (int64_t)o * HW;
+  auto load = [&](int64_t q, float(&g)[U], float(&yv)[U], float(&v)[U][NT]) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const bool in = (IT)q + 256 * u < (IT)npix;
       const IT gb = in ? go + (IT)(rw + j) * 4 : Plane<IT>::kOutRow;
-#pragma unroll
-      for (int k = 0; k < OT; ++k) {
-        const int64_t ch = (int64_t)(o0 + k < O ? o0 + k : O - 1) * HW;
-        g[u][k] = Plane<IT>(dy + ch, npix * O - ch).get(gb);
-        yv[u][k] = RELU ? Plane<IT>(y + ch, npix * O - ch).get(gb) : 1.f;
-      }
+      g[u] = Plane<IT>(dy + ch, npix * O - ch).get(gb);
+      yv[u] = RELU ? Plane<IT>(y + ch, npix * O - ch).get(gb) : 1.f;
       // the pixel's own row is in the image; the ones drow away are if they do not leave [0, HW)
       const IT xb = in ? xo : Plane<IT>::kOutRow;
       const IT co[3] = {j >= dcol ? (IT)(j - dcol) * 4 : Plane<IT>::kOutCol, (IT)j * 4,
@@ -248,19 +241,17 @@ __global__ __launch_bounds__(256) void k_conv_bwd_filter(const float* __restrict
       }
     }
   };
-  auto add = [&](const float(&dv)[U][OT], const float(&yv)[U][OT], const float(&v)[U][NT]) {
+  auto add = [&](const float(&dv)[U], const float(&yv)[U], const float(&v)[U][NT]) {
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int u = 0; u < U; ++u) {
+      const float g = yv[u] > 0.f ? dv[u] : 0.f;
+      ab += g;
 #pragma unroll
-      for (int k = 0; k < OT; ++k) {
-        const float g = yv[u][k] > 0.f ? dv[u][k] : 0.f;
-        ab[k] += g;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) acc[k][t] = __builtin_fmaf(g, v[u][t], acc[k][t]);
-      }
+      for (int t = 0; t < NT; ++t) acc[t] = __builtin_fmaf(g, v[u][t], acc[t]);
+    }
   };
   // two sets of registers: the next U pixels load while the current ones are added
-  float g0[U][OT], y0[U][OT], v0[U][NT], g1[U][OT], y1[U][OT], v1[U][NT];
+  float g0[U], y0[U], v0[U][NT], g1[U], y1[U], v1[U][NT];
   load(threadIdx.x, g0, y0, v0);
   for (int64_t q = threadIdx.x; q < npix; q += 512 * U) {
     load(q + 256 * U, g1, y1, v1);
@@ -271,28 +262,22 @@ __global__ __launch_bounds__(256) void k_conv_bwd_filter(const float* __restrict
     add(g1, y1, v1);
   }
 #pragma unroll
-  for (int k = 0; k < OT; ++k)
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-      if (!__builtin_isfinite(acc[k][t]) && o0 + k < O)
-        acc[k][t] = filter_masked<RELU>(x, dy, y, B, C, O, H, W, dil, c, o0 + k, t0 + t, threadIdx.x);
+  for (int t = 0; t < NT; ++t)
+    if (!__builtin_isfinite(acc[t]))
+      acc[t] = filter_masked<RELU>(x, dy, y, B, C, O, H, W, dil, c, o, t0 + t, threadIdx.x);
   // the tree over the chains: 128, 64, then 32 .. 1 apart
-  constexpr int NR = OT * (NT + 1);
+  constexpr int NR = NT + 1;
   __shared__ float red[NR][256];
 #pragma unroll
-  for (int k = 0; k < OT; ++k) {
-#pragma unroll
-    for (int t = 0; t < NT; ++t) red[k * (NT + 1) + t][threadIdx.x] = acc[k][t];
-    red[k * (NT + 1) + NT][threadIdx.x] = ab[k];
-  }
+  for (int t = 0; t < NT; ++t) red[t][threadIdx.x] = acc[t];
+  red[NT][threadIdx.x] = ab;
   __syncthreads();
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  for (int r = wv; r < NR; r += 4) {
-    float s = (red[r][lane] + red[r][lane + 128]) + (red[r][lane + 64] + red[r][lane + 192]);
+  for (int t = wv; t < NR; t += 4) {
+    float s = (red[t][lane] + red[t][lane + 128]) + (red[t][lane + 64] + red[t][lane + 192]);
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) s += __shfl_down(s, d);
-    const int o = o0 + r / (NT + 1), t = r % (NT + 1);
-    if (lane == 0 && o < O) {
+    if (lane == 0) {
       if (t < NT) dw[((int64_t)o * C + c) * 9 + t0 + t] = s;
       else if (c == 0 && tg == 0) db[o] = s;
     }
@@ -444,12 +429,12 @@ void conv_launch(const float* in, const float* act, const float* w, const float*
 #undef RKS_CONV
 }
 
-template <int OT, int NT, int U>
+template <int NT, int U>
 void filter_launch_t(const float* x, const float* dy, const float* y, float* dw, float* db, int B, int C, int O, int H,
                      int W, int dil, int relu, hipStream_t st) {
-  const unsigned grid = (unsigned)((O + OT - 1) / OT * C * (9 / NT));
+  const unsigned grid = (unsigned)(O * C * (9 / NT));
   const bool small = (int64_t)B * H * W * (C > O ? C : O) < ((int64_t)1 << 28);
-#define RKS_FILT_K(R, IT, T) k_conv_bwd_filter<OT, NT, U, R, IT, T><<<grid, 256, 0, st>>>(x, dy, y, dw, db, B, C, O, H, W, dil)
+#define RKS_FILT_K(R, IT, T) k_conv_bwd_filter<NT, U, R, IT, T><<<grid, 256, 0, st>>>(x, dy, y, dw, db, B, C, O, H, W, dil)
   if (!small) {
     if (relu) RKS_FILT_K(true, uint64_t, true);
     else RKS_FILT_K(false, uint64_t, true);
@@ -475,9 +460,9 @@ void filter_launch_t(const float* x, const float* dy, const float* y, float* dw,
 void filter_launch(const float* x, const float* dy, const float* y, float* dw, float* db, int B, int C, int O, int H,
                    int W, int dil, int relu, hipStream_t st) {
   if ((int64_t)C * O >= 128)
-    filter_launch_t<1, 9, 4>(x, dy, y, dw, db, B, C, O, H, W, dil, relu, st);
+    filter_launch_t<9, 4>(x, dy, y, dw, db, B, C, O, H, W, dil, relu, st);
   else
-    filter_launch_t<1, 3, 4>(x, dy, y, dw, db, B, C, O, H, W, dil, relu, st);
+    filter_launch_t<3, 4>(x, dy, y, dw, db, B, C, O, H, W, dil, relu, st);
 }
 
 // A dilation that leaves the image in any case: every one from max(H, W) on is the same, and stays in range here.

@@ -356,10 +356,10 @@ int arnoldi_step_ks(rks_ctx* c, int t) {
   }
   {
     Prof p(c, CAT_UPDATE, timed);
-    int G = rks::launch_dots(e, ncol, c->U, c->ldu, c->w, 0, c->kpart);
+    int G = rks::launch_dots(e, ncol, c->U, c->ldu, c->w, c->kpart);
     rks::launch_reduce_len(e, c->kpart, G, c->z, ncol);
     rks::launch_update(e, ncol, c->U, c->ldu, c->w, c->cs, c->z, c->cs + t, c->sr, 0, unew, c->spart);
-    G = rks::launch_dots(e, ncol, c->U, c->ldu, unew, 1, c->kpart);
+    G = rks::launch_dots(e, ncol, c->U, c->ldu, unew, c->kpart);
     rks::launch_reduce_len(e, c->kpart, G, c->z, ncol);
     const int Gs = rks::launch_update(e, ncol, c->U, c->ldu, unew, c->cs, c->z, nullptr, c->sr, 1, unew, c->spart);
     rks::launch_ks_finalize(e, t, c->sr, c->spart, Gs, c->B, c->m + 1, c->cs, c->flags, kBreakdownRel);

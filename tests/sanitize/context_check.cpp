@@ -135,7 +135,7 @@ int launch_resid(const LaunchEnv& e, int64_t, const double* X, int ke, const int
 void launch_normalise(const LaunchEnv&, double*, int, const int*, const double*) {}
 void launch_copy16(hipStream_t, const void*, void*, int64_t) {}
 void launch_read16(hipStream_t, const void*, int64_t) {}
-int launch_dots(const LaunchEnv&, int, const void*, int64_t, const void*, int, double*) { return 1; }
+int launch_dots(const LaunchEnv&, int, const void*, int64_t, const void*, double*) { return 1; }
 void launch_reduce_len(const LaunchEnv&, const double*, int, double*, int) {}
 void launch_ks_finalize(const LaunchEnv&, int, const double*, const double*, int, double*, int, double*, int*, double) {}
 void launch_ks_start(const LaunchEnv&, const double*, double*) {}
