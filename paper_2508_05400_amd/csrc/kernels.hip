@@ -1954,7 +1954,7 @@ __global__ __launch_bounds__(256) void k_gauss_sketch(int64_t n, const TX* __res
   __shared__ double acc[4][2][64], accy[HY ? 4 : 1][2][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int np = (sp.d + 1) >> 1;
-  const int p = (int)blockIdx.y * 64 + lane;
+  const int p = (int)blockIdx.y * 64 + lane, pc = p < np ? p : np - 1;
   const int64_t r0 = (int64_t)blockIdx.x * R;
   const int64_t rend = min(n, r0 + R);
   const int64_t Rw = (R + 3) >> 2;
@@ -1965,8 +1965,9 @@ __global__ __launch_bounds__(256) void k_gauss_sketch(int64_t n, const TX* __res
     const double xv = HX && i < a1 ? Conv<TX>::ld(x[i]) : 0.0;
     const double yv = HY && i < a1 ? Conv<TY>::ld(y[i]) : 0.0;
     const int cnt = (int)min((int64_t)64, a1 - c);
-    // row c + j: x and y of it are read from lane j, which all lanes do (a lane
-    // without a pair holds values of the 64 rows, too)
+    // row c + j: x and y of it are read from lane j.  All lanes take part: one
+    // without a pair of its own (p >= np) holds values of the 64 rows, too, and
+    // goes through the last pair's sums, which it does not store
     auto row_x = [&](int j) { return HX ? readlane_f64(xv, j) : 0.0; };
     auto row_y = [&](int j) { return HY ? readlane_f64(yv, j) : 0.0; };
     auto add = [&](double v, double u, double g0, double g1) {
@@ -1981,7 +1982,7 @@ __global__ __launch_bounds__(256) void k_gauss_sketch(int64_t n, const TX* __res
     };
     if constexpr (OM) {
       typedef double d2v __attribute__((ext_vector_type(2)));
-      const d2v* col = (const d2v*)om + c * np + (p < np ? p : np - 1);
+      const d2v* col = (const d2v*)om + c * np + pc;
       for (int j0 = 0; j0 < cnt; j0 += kGsU) {
         d2v g[kGsU];
 #pragma unroll
@@ -1992,12 +1993,9 @@ __global__ __launch_bounds__(256) void k_gauss_sketch(int64_t n, const TX* __res
       }
     } else {
       for (int j = 0; j < cnt; ++j) {
-        const double v = row_x(j), u = row_y(j);
-        if (p < np) {
-          double g0, g1;
-          gauss_pair((uint64_t)(c + j), (uint32_t)p, 0u, sp.k0, sp.k1, g0, g1);
-          add(v, u, g0, g1);
-        }
+        double g0, g1;
+        gauss_pair((uint64_t)(c + j), (uint32_t)pc, 0u, sp.k0, sp.k1, g0, g1);
+        add(row_x(j), row_y(j), g0, g1);
       }
     }
   }
