@@ -1083,16 +1083,17 @@ struct ColPk {
 // Each thread owns V consecutive rows and streams every basis column once
 // with one 16-byte load per column (plain for the first nkeep columns, non-
 // temporal for the others, see kept_columns; the up to 7 columns left over by
-// the groups are always plain), in groups of 8 (8 loads, then their FMAs).  ROLL: a rolling window of 8 instead, where the slot of
-// column l is refilled with column l + 8 as soon as it is consumed.  Measured:
-// the window pays in k_ls_update without its prefetch when each thread walks
-// 4 or more packets (one 16-wave workgroup per CU; 393 -> 364 us per launch
-// on the 160^3 operator in FP64, 212 -> 198 us in FP32) and costs 1-8% with 1
-// or 2 packets per thread and in k_update (more waves per CU), which keep the
-// groups.  Either way the columns are added in order, one FMA chain per row,
-// so both give the same bits.  The coefficients are wave-uniform.  Padding rows (>= n, < ldu)
-// are zero in U and w, so packets may run past n; they stay zero and are
-// left out of the sketch.
+// the groups are always plain), in groups of 8 (8 loads, then their FMAs).
+// ROLL: a rolling window of 8 instead, where the slot of column l is refilled
+// with column l + 8 as soon as it is consumed.  Measured: the window pays in
+// k_ls_update without its prefetch when each thread walks 4 or more packets
+// (one 16-wave workgroup per CU; 393 -> 364 us per launch on the 160^3
+// operator in FP64, 212 -> 198 us in FP32) and costs 1-8% with 1 or 2 packets
+// per thread and in k_update (more waves per CU), which keep the groups.
+// Either way the columns are added in order, one FMA chain per row, so both
+// give the same bits.  The coefficients are wave-uniform.  Padding rows (>=
+// n, < ldu) are zero in U and w, so packets may run past n; they stay zero
+// and are left out of the sketch.
 template <typename TV, typename TW, int KIND, int NPRE = 0, bool PREW = false, int PB = 16, bool ROLL = false,
           bool SPLIT = false>
 __device__ __forceinline__ void update_body(int64_t n, int64_t npk, int ncol, const TV* __restrict__ U, int64_t ldu,
@@ -1776,11 +1777,12 @@ __global__ __launch_bounds__(256) void k_interleave(int64_t n, const double* __r
 // interleaved Xi, so that a gather is one 64-byte piece for all the columns
 // instead of a line for each.  A slot owns the rows that start in its equal
 // share of nonzeros and rows together (resid_row_at; by nonzeros alone, one
-// slot owns a whole run of empty rows) and walks their nonzeros as one sequence, kResidU
-// loads and gathers at a time, whatever the rows' lengths (one row per slot
-// with a common trip count waits for the longest of 8: 1.54 ms for 8 columns
-// of the 2M-row power-law operator against 0.92, 4.8 TB/s of 128-byte lines).  A row's products are added in
-// order.  The other column of a complex pair is the neighbouring lane's.
+// slot owns a whole run of empty rows) and walks their nonzeros as one
+// sequence, kResidU loads and gathers at a time, whatever the rows' lengths
+// (one row per slot with a common trip count waits for the longest of 8: 1.54
+// ms for 8 columns of the 2M-row power-law operator against 0.92, 4.8 TB/s of
+// 128-byte lines).  A row's products are added in order.  The other column of
+// a complex pair is the neighbouring lane's.
 constexpr int kResidU = 8;
 
 __global__ __launch_bounds__(256) void k_resid_csr(const int* __restrict__ rp, const int* __restrict__ col,
@@ -2223,26 +2225,28 @@ void launch_ls(const LaunchEnv& e, int t, int pending, int finalize_only, const 
 }
 
 // Leading basis columns that a pass over ncol of them reads with plain loads,
-// so that they stay in the 256 MB Infinity Cache until the next step's pass (a
-// multiple of 8, the groups of the column walk); the other groups are read non-
-// temporally and leave the cache alone (the fewer than 8 columns after the last
-// group of the update, and the leading ones that k_ls_update prefetches, are
-// plain whatever this rule says).  ncol counts the column that the step writes.  Reading every column non-temporally
-// puts the whole pass on HBM; reading more of them plainly than fit evicts
-// each before it is read again (least recently used over a cyclic walk), and
-// A, x and w want a share too.  All are kept up to 320 MB (a step's later
-// columns then still find most of the earlier ones), beyond that about 160 MB
-// of them.  Measured, microseconds per launch, all non-temporal / this rule /
-// 200 MB kept / all plain: 777^2 FP64 (m = 60) 45.2 / 38.8 / 38.8 / 38.8; 1000^2
+// so that they stay in the 256 MB Infinity Cache until the next step's pass
+// (a multiple of 8, the groups of the column walk); the other groups are read
+// non-temporally and leave the cache alone (the fewer than 8 columns after
+// the last group of the update, and the leading ones that k_ls_update
+// prefetches, are plain whatever this rule says).  ncol counts the column
+// that the step writes.  Reading every column non-temporally puts the whole
+// pass on HBM; reading more of them plainly than fit evicts each before it is
+// read again (least recently used over a cyclic walk), and A, x and w want a
+// share too.  All are kept up to 320 MB (a step's later columns then still
+// find most of the earlier ones), beyond that about 160 MB of them.
+// Measured, microseconds per launch, all non-temporal / this rule / 200 MB
+// kept / all plain: 777^2 FP64 (m = 60) 45.2 / 38.8 / 38.8 / 38.8; 1000^2
 // FP64 59.2 / 54.5 / 54.2 / 62.7; 101^3 FP64 (m = 90) 90.8 / 82.3 / 83.9 /
-// 88; 101^3 pair 74.4 / 73.3 / 74.1 / 80; deterministic Krylov-Schur on 300,000 rows
-// (m = 80) update 23.9 / 20.3, dots 34.2 / 24.2; on 10^6 rows 67.6 / 62.5 and
-// 63.1 / 61.4.  The rolling window keeps none: its columns are 13 MB or more,
-// and keeping 8 of them gained nothing (128^3, 2 10^6 rows) or cost the SpMV
-// more than it gained (160^3: 326 to 322, SpMV 49 to 53).  A BF16 basis beyond
-// 320 MB keeps none either: its conversions, not HBM, bound the update (160^3:
-// 113 us without, 114 with 160 MB kept), and the SpMV's operands get the cache
-// (44 and 51 us; a bounded solve 96.9 and 98.0 ms, 128^3 55.7 and 55.8).
+// 88; 101^3 pair 74.4 / 73.3 / 74.1 / 80; deterministic Krylov-Schur on
+// 300,000 rows (m = 80) update 23.9 / 20.3, dots 34.2 / 24.2; on 10^6 rows
+// 67.6 / 62.5 and 63.1 / 61.4.  The rolling window keeps none: its columns
+// are 13 MB or more, and keeping 8 of them gained nothing (128^3, 2 10^6
+// rows) or cost the SpMV more than it gained (160^3: 326 to 322, SpMV 49 to
+// 53).  A BF16 basis beyond 320 MB keeps none either: its conversions, not
+// HBM, bound the update (160^3: 113 us without, 114 with 160 MB kept), and
+// the SpMV's operands get the cache (44 and 51 us; a bounded solve 96.9 and
+// 98.0 ms, 128^3 55.7 and 55.8).
 static int kept_columns(const LaunchEnv& e, int ncol) {
   const double col = (double)e.n * (e.prec == 3 ? 6 : e.vbytes());
   if (ncol * col <= 320e6) return (ncol + 7) & ~7;

@@ -6,8 +6,10 @@
 //   k_ls_update    every workgroup: finalise the previous column (beta, s,
 //                  B(t,t-1)) and solve the FP64 least squares h = S^+ z  (Algorithm 2: low-dimensional projection);
 //                  then u~ = w - U_t h, stored, and partial sums of Omega u~ (Algorithm 2: update in R^n, its sketch)
-// (k_ls alone finalises the last column of an extension; k_update alone
-// serves the deterministic Krylov-Schur step.)
+// (A Gaussian Omega takes a launch of its own, k_gauss_sketch, after the
+// product, for w and the pending column together; k_ls alone finalises the
+// last column of an extension; k_update serves the deterministic Krylov-Schur
+// step.)
 // The new column is kept unnormalised; its scale 1/beta is folded into the
 // next step's coefficients (lazy normalisation saves one pass over n).
 // k_rotate applies the restart rotation U <- U Y (Algorithm 1, truncation).
