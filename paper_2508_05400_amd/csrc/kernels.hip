@@ -2422,19 +2422,18 @@ void launch_rotate(const LaunchEnv& e, const void* U, int64_t ldu, int in0, int 
 }
 
 // Whether nc columns outside the sliced layout take one SpMV each and a pass
-// over the products, instead of one walk of A for all of them (k_resid_csr).
-// Few columns do: the walk's time hardly depends on their number.  Measured,
-// microseconds of rks_eigpairs with 2, 3 and 4 columns by products / by a
-// walk: 20,000 power-law rows 57, -, 82 / 102; 150,001 rows 85, 110, 137 / 172;
-// 2M rows in column blocks 594, 844, 1,117 / 1,035.  So do matrices with a row
-// that one slot walks (0.11 us a nonzero) longer than the walk of all the
-// others takes; the SpMV gives such a row a whole wave.  7 columns
-// and one row of L nonzeros among power-law rows, by products / by a walk:
-// 150,001 rows, L = 1,200 - / 240, L = 2,400 232 / 381, L = 150,000 5,530 /
-// 16,900; 2M rows, L = 5,000 - / 1,281, L = 80,000 7,940 / 10,100.
-// The walk also needs the whole scratch (kResidV columns).
+// over the products, instead of one walk of A for all of them (k_resid_csr;
+// it also needs the whole scratch, kResidV columns).  The walk takes 27 ps a
+// nonzero whatever nc is and 0.11 us a nonzero of the longest row, which one
+// slot walks; a product takes 11 us and 7.5 ps a nonzero (in units of 0.11 us
+// below), with a whole wave for a long row.  Measured, microseconds of
+// rks_eigpairs by products / by a walk: 2 columns, 200 power-law rows 60 / 47,
+// 1,000 rows 58 / 90, 150,001 rows 85 / 172, 2M rows 594 / 1,035; 4 columns,
+// 150,001 rows 137 / 172, 2M rows 1,117 / 1,035; 6 columns, 5,003 rows 110 /
+// 96; 7 columns and one row of L nonzeros, 150,001 rows, L = 2,400 232 / 381,
+// L = 150,000 5,530 / 16,900; 2M rows, L = 80,000 7,940 / 10,100.
 static bool resid_by_products(const LaunchEnv& e, int64_t nnz, int nc, int xcols) {
-  return nc <= (e.cb ? 3 : 4) || xcols < kResidV || e.longest > kTileFill + nnz / 2048;
+  return xcols < kResidV || nc * (100 + nnz / 14336) < e.longest + nnz / 4096;
 }
 
 int launch_resid(const LaunchEnv& e, int64_t nnz, const double* X, int ke, const int* kind, const double* re,
