@@ -1455,7 +1455,9 @@ int rks_create(const rks_csr* A, int32_t k, int32_t m, int32_t d, int32_t which,
     e.xcur = c->xcur;
   }
   e.rp = c->rp;
-  for (int64_t r = 0; r < n; ++r) e.longest = std::max(e.longest, rp[r + 1] - rp[r]);
+  int longest = 0;
+  for (int64_t r = 0; r < n; ++r) longest = std::max(longest, rp[r + 1] - rp[r]);
+  e.longest = longest;
   e.col = c->col;
   e.val = c->val;
   e.val32 = c->val32;
